@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/sigkernel.h"
@@ -338,8 +339,10 @@ struct GradPlan {
   int nb_max, nseg_max;
   int64_t cols_max;
   int32_t mrows, nrows;
-  int64_t slot_stride;  // doubles
-  size_t order, counts, scratch, partx, party, total;
+  int64_t slot_stride;  // doubles (the larger of the two kernels')
+  int R, ng;            // the reversing kernel's rows per lane and pairs per wave
+  int rev_nb_max, rev_nck_max, rev_ck_every;
+  size_t order, counts, redo, scratch, partx, party, total;
 };
 
 // Pairs per gradient task for a uniform y batch: the tuned value, else about
@@ -367,12 +370,46 @@ GradPlan grad_plan(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, uint32_
   const int d = X0->dim;
   P.mrows = (int32_t)m;
   P.nrows = (int32_t)n;
+  P.R = sk::kGradRows;
+  P.ng = 1;
   if (P.ragged) {
     P.run = 1;
     P.runs_per_row = Y0->n_paths;
   } else {
     const sk_tune t = sk::tuning_for(SK_OP_GRAM_BACKWARD, X0, Y0, lam0, flags);
-    P.run = choose_grad_run(X0->n_paths, Y0->n_paths, (flags & SK_SYMMETRIC) != 0, t.run);
+    // Rows per lane and pairs per wave by the least modelled time of the
+    // busiest SIMD: a task sweeps its bands in columns + lanes - 1 steps of
+    // cost R + 3 each (a step's instructions that do not grow with R weigh
+    // like three rows), and a SIMD with a single wave issues at 0.7 of its rate.
+    const int64_t M = m << P.lam;
+    const bool sym = (flags & SK_SYMMETRIC) != 0;
+    const int64_t pairs = sym ? X0->n_paths * (X0->n_paths + 1) / 2 : X0->n_paths * Y0->n_paths;
+    double best = 0.0;
+    for (int R : {4, 8}) {
+      for (int ng : {1, 2, 4}) {
+        if (ng > 1 && (t.run > 0 || 64 / ng * (int64_t)R < M)) continue;
+        if (!sk::grad_rev_fn(P.lam, R, ng, d, true)) continue;
+        const int64_t run = ng > 1 || n < sk::grad_rev_segment(P.lam)
+                                ? 1
+                                : choose_grad_run(X0->n_paths, Y0->n_paths, sym, t.run);
+        const int64_t nb = (M + 64 / ng * (int64_t)R - 1) / (64 / ng * (int64_t)R);
+        const int64_t tasks = (pairs + ng * run - 1) / (ng * run);
+        const double task = (double)nb * (double)(run * n + 64 / ng - 1) * (R + 3);
+        const int64_t per_simd = (tasks + kSimds - 1) / kSimds;
+        const double cost = (double)per_simd * task / (per_simd == 1 ? 0.7 : 1.0);
+        if (best == 0.0 || cost < best) {
+          best = cost;
+          P.R = R;
+          P.ng = ng;
+        }
+      }
+    }
+    if (P.ng > 1)
+      P.run = P.ng < Y0->n_paths ? P.ng : (Y0->n_paths > 0 ? Y0->n_paths : 1);
+    else
+      P.run = choose_grad_run(X0->n_paths, Y0->n_paths, sym, t.run);
+    // the reversing kernel saves one pair end per lane and segment
+    if (P.ng == 1 && n < sk::grad_rev_segment(P.lam)) P.run = 1;
     P.runs_per_row = (Y0->n_paths + P.run - 1) / P.run;
   }
   P.n_tasks = X0->n_paths * P.runs_per_row;
@@ -384,12 +421,24 @@ GradPlan grad_plan(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, uint32_
   P.cols_max = P.run * (n > 0 ? n : 1);
   const int C = sk::grad_segment(P.lam, d);
   P.nseg_max = (int)((P.cols_max + 63 + C - 1) / C);
-  P.slot_stride = sk::grad_slot_layout(P.lam, P.nb_max, P.nseg_max, P.cols_max).stride;
+  const int64_t rev_rows = 64 / P.ng * (int64_t)P.R;
+  P.rev_nb_max = (int)(M > 0 ? (M + rev_rows - 1) / rev_rows : 1);
+  const int64_t rev_cols = P.ng > 1 ? (n > 0 ? n : 1) : P.cols_max;
+  const int RC = sk::grad_rev_segment(P.lam);
+  const int rev_nseg = (int)((rev_cols + 64 / P.ng - 1 + RC - 1) / RC);
+  P.rev_ck_every = sk::grad_rev_ck_every(rev_nseg);
+  P.rev_nck_max = (rev_nseg + P.rev_ck_every - 1) / P.rev_ck_every;
+  P.slot_stride = std::max(
+      sk::grad_slot_layout(P.lam, P.nb_max, P.nseg_max, P.cols_max).stride,
+      sk::grad_rev_slot_layout(P.R, P.lam, P.rev_nb_max, P.rev_nck_max, P.cols_max,
+                               P.ng > 1 ? 1 : P.run).stride);
   size_t off = forward_ws(&Xr, &Yr);
   P.order = off;
   if (P.ragged) off += align256((size_t)(P.n_tasks > 0 ? P.n_tasks : 1) * sizeof(int32_t));
   P.counts = off;
-  off += 256;  // the pair plan's counts and counters, the gradient queue head
+  off += 256;  // the pair plan's counts and counters, the gradient queue heads
+  P.redo = off;
+  off += align256((size_t)(P.n_tasks > 0 ? P.n_tasks : 1) * sizeof(int32_t));
   P.scratch = off;
   off += align256((size_t)P.slots * (size_t)P.slot_stride * sizeof(double));
   P.partx = off;
@@ -1407,7 +1456,16 @@ static sk_status gram_backward(const sk_paths* X, const sk_paths* Y, int32_t dya
   ga.part_y = ys ? reinterpret_cast<double*>(base + P.party) : nullptr;
   ga.mrows = P.mrows;
   ga.nrows = P.nrows;
-  if (sk::launch_grad(ga, lam, d, ys, P.slots, st) != hipSuccess) return SK_ERR_HIP;
+  // the reversing kernel over every task, then the recomputing one over the
+  // tasks it listed
+  ga.redo = reinterpret_cast<int32_t*>(base + P.redo);
+  ga.redo_count = counts + 6;
+  sk::GradArgs gf = ga;
+  gf.nb_max = P.rev_nb_max;
+  gf.ck_every = P.rev_ck_every;
+  gf.nck_max = P.rev_nck_max;
+  ga.counter = counts + 5;
+  if (sk::launch_grad(gf, ga, P.R, P.ng, lam, d, ys, P.slots, st) != hipSuccess) return SK_ERR_HIP;
 
   // the parts of a refined increment are the increment over rep: their
   // gradients sum, times 1 / rep, to the increment's

@@ -19,6 +19,25 @@ void* grad_fn(int lam, int d, bool ys) {
   }
 }
 
+#define SK_DECL(l, r, g) void* grad_rev_fn_l##l##_r##r##_g##g(int d, bool ys);
+#define SK_DECL_R(l, r) SK_DECL(l, r, 1) SK_DECL(l, r, 2) SK_DECL(l, r, 4)
+SK_DECL_R(0, 4) SK_DECL_R(1, 4) SK_DECL_R(2, 4) SK_DECL_R(3, 4)
+SK_DECL_R(0, 8) SK_DECL_R(1, 8) SK_DECL_R(2, 8)
+#undef SK_DECL_R
+#undef SK_DECL
+
+void* grad_rev_fn(int lam, int R, int ng, int d, bool ys) {
+  using Pick = void* (*)(int, bool);
+#define SK_ROW(l, r) {grad_rev_fn_l##l##_r##r##_g1, grad_rev_fn_l##l##_r##r##_g2, grad_rev_fn_l##l##_r##r##_g4}
+  static const Pick r4[4][3] = {SK_ROW(0, 4), SK_ROW(1, 4), SK_ROW(2, 4), SK_ROW(3, 4)};
+  static const Pick r8[3][3] = {SK_ROW(0, 8), SK_ROW(1, 8), SK_ROW(2, 8)};
+#undef SK_ROW
+  const int g = ng == 1 ? 0 : ng == 2 ? 1 : ng == 4 ? 2 : -1;
+  if (lam < 0 || lam > 3 || g < 0) return nullptr;
+  if (R == 4) return r4[lam][g](d, ys);
+  return R == 8 && lam < 3 ? r8[lam][g](d, ys) : nullptr;
+}
+
 namespace {
 
 __global__ void zero_i32_kernel(int32_t* p, int n) {
@@ -106,16 +125,20 @@ __global__ __launch_bounds__(256) void grad_points_kernel(const GradPointArgs a)
 
 bool grad_supported(int lam, int d) { return grad_fn(lam, d, true) != nullptr; }
 
-hipError_t launch_grad(const GradArgs& a, int lam, int d, bool ys, int64_t slots,
-                       hipStream_t stream) {
-  auto f = reinterpret_cast<void (*)(const GradArgs)>(grad_fn(lam, d, ys));
-  if (!f) return hipErrorInvalidValue;
-  if (a.n_tasks <= 0 || slots <= 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, stream, a.counter, 1);
+hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng, int lam, int d,
+                       bool ys, int64_t slots, hipStream_t stream) {
+  auto f = reinterpret_cast<void (*)(const GradArgs)>(grad_rev_fn(lam, R, ng, d, ys));
+  auto g = reinterpret_cast<void (*)(const GradArgs)>(grad_fn(lam, d, ys));
+  if (!f || !g) return hipErrorInvalidValue;
+  if (fast.n_tasks <= 0 || slots <= 0) return hipSuccess;
+  // both queue heads and the redo count
+  hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, stream, fast.counter, kGradCounters);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   // one wave per workgroup: slot = workgroup; every slot's scratch is its own,
   // so any number of them may be resident at once
-  hipLaunchKernelGGL(f, dim3((unsigned)slots), dim3(64), 0, stream, a);
+  hipLaunchKernelGGL(f, dim3((unsigned)slots), dim3(64), 0, stream, fast);
+  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+  hipLaunchKernelGGL(g, dim3((unsigned)slots), dim3(64), 0, stream, redo);
   return hipGetLastError();
 }
 

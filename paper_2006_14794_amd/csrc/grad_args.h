@@ -32,10 +32,17 @@ struct GradArgs {
   int64_t slot_stride;
   int32_t nb_max;           // row bands of the tallest x path
   int32_t nseg_max;         // segments of the longest task
+  int32_t ck_every;         // reversing kernel: segments per checkpoint,
+  int32_t nck_max;          // ... and checkpoints of the longest task
   int64_t cols_max;         // coarse columns of the longest task
   double* part_x;           // [nx][runs_per_row][mrows][dim]: x-side increment gradients
   double* part_y;           // [nx][ny][nrows][dim]: y-side increment gradients
   int32_t mrows, nrows;     // x_len - 1, y_len - 1
+  // tasks whose rebuilt forward nodes differed too much (grad_rev_kernel.h):
+  // that kernel appends them here, and grad_kernel.h takes its tasks from this
+  // list alone (nullptr there: all n_tasks tasks)
+  int32_t* redo;
+  int32_t* redo_count;      // zeroed before the launches
 };
 
 // Fine rows per lane of the gradient kernel: bands of 64 R rows.
@@ -88,6 +95,55 @@ __host__ __device__ inline GradSlot grad_slot_layout(int lam, int nb_max, int ns
   s.hand_a = s.hand_f + (int64_t)(nb_max - 1) * cols_max * S;
   s.stride = s.hand_a + 2 * (cols_max + 1) * (S + 1);
   s.stride = (s.stride + 31) & ~int64_t(31);  // 256-byte aligned slots
+  return s;
+}
+
+// ---- the reversing kernel (grad_rev_kernel.h) ----
+// Compiled rows per lane R: 4 always, 8 where the increments and accumulators
+// of the 8 / 2^lam coarse rows leave two waves per SIMD.
+__host__ __device__ constexpr bool grad_rev_fits(int R, int lam, int d) {
+  if (R == 4) return true;
+  return R == 8 && lam <= 2 && (8 >> lam) * d <= 16;
+}
+// Steps per segment of the staging.  Even, at most 32 (the pair-end masks).
+__host__ __device__ constexpr int grad_rev_segment(int lam) {
+  return lam == 0 ? 32 : lam == 1 ? 24 : lam == 2 ? 16 : 8;
+}
+// Segments between two checkpoints (R + 2^lam + 1 doubles per lane): at most
+// four, and at least eight checkpoints over the longest task's columns, which
+// bounds the region over which the rebuilt nodes drift.
+__host__ __device__ constexpr int grad_rev_ck_every(int nseg_max) {
+  return nseg_max >= 32 ? 4 : nseg_max >= 16 ? nseg_max / 8 : 1;
+}
+// Two waves per SIMD (256 registers) where the increments, their double
+// accumulators and the y-side sums leave room for the sweep's state; else one
+// or two, as the registers allow.
+__host__ __device__ constexpr int grad_rev_waves(int R, int lam, int d) {
+  return 3 * ((R >> lam) > 0 ? (R >> lam) : 1) * d + 4 * d <= 64 && lam < 3 ? 2 : 1;
+}
+__host__ __device__ constexpr int grad_rev_state_doubles(int R, int lam) {
+  return R + (1 << lam) + 1;
+}
+
+// Scratch of one wave slot, in doubles:
+//   ckpt    [nb_max][nck_max][state][64 lanes]    the state after every ck_every segments
+//   hand_f  [nb_max][cols_max << lam]             bottom rows of the bands
+//   hand_a  [2][cols_max + 1][2^lam + 1]          as in GradSlot
+//   pend    [nb_max][pairs][R + 1][64 lanes]      the strips' nodes at the pairs' last columns
+struct GradRevSlot {
+  int64_t ckpt, hand_f, hand_a, pend, stride;
+};
+__host__ __device__ inline GradRevSlot grad_rev_slot_layout(int R, int lam, int nb_max,
+                                                            int nck_max, int64_t cols_max,
+                                                            int64_t pairs) {
+  GradRevSlot s{};
+  const int64_t S = int64_t(1) << lam;
+  s.ckpt = 0;
+  s.hand_f = (int64_t)nb_max * nck_max * grad_rev_state_doubles(R, lam) * 64;
+  s.hand_a = s.hand_f + (int64_t)nb_max * cols_max * S;
+  s.pend = s.hand_a + 2 * (cols_max + 1) * (S + 1);
+  s.stride = s.pend + (int64_t)nb_max * pairs * (R + 1) * 64;
+  s.stride = (s.stride + 31) & ~int64_t(31);
   return s;
 }
 

@@ -160,11 +160,14 @@ __attribute__((amdgpu_waves_per_eu(D <= 4 && LAM < 3 ? 2 : 1, 2))) void grad_ker
   const int64_t hf_band = a.cols_max * S;
   const int64_t ha_buf = (a.cols_max + 1) * (S + 1);
 
+  const int32_t n_tasks = a.redo ? *a.redo_count : a.n_tasks;
+  if (n_tasks == 0) return;
   for (;;) {
     int32_t task = 0;
     if (lane == 0) task = atomicAdd(a.counter, 1);
     task = __builtin_amdgcn_readlane(task, 0);  // scalar: uniform loop control
-    if (task >= a.n_tasks) break;
+    if (task >= n_tasks) break;
+    if (a.redo) task = __builtin_amdgcn_readfirstlane(a.redo[task]);
     int64_t ia, b0, b1, jslot;
     if (a.order) {
       const int64_t pid = a.order[task];

@@ -85,12 +85,19 @@ hipError_t launch_lifted(const SweepArgs& a, int lam, int rows_per_lane, int dim
 // rows (0 if none).
 int choose_rows_for(int kind, int64_t fine_rows, int lam, int dim);
 
-// Gradient of weighted Gram entries (grad_kernel.h, grad.hip): persistent
-// waves over the tasks of a GradArgs, `slots` of them, each with its own
-// scratch slot (the queue counter is zeroed by a kernel first); ys: form the
-// y-side gradients (a.part_y), else the x side only.
-hipError_t launch_grad(const GradArgs& a, int lam, int dim, bool ys, int64_t slots,
-                       hipStream_t stream);
+// Gradient of weighted Gram entries (grad_rev_kernel.h, grad_kernel.h,
+// grad.hip): persistent waves over the tasks, `slots` of them, each with its
+// own scratch slot.  `fast` runs every task on the reversing kernel with R rows
+// per lane and ng pairs per wave; `redo` then runs the tasks of its list on
+// the recomputing one.  The kGradCounters queue heads at fast.counter (fast's,
+// redo's, the list's length) are zeroed by a kernel first.  ys: form the
+// y-side gradients (part_y), else the x side only.
+constexpr int kGradCounters = 3;
+hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng, int lam, int dim,
+                       bool ys, int64_t slots, hipStream_t stream);
+// The reversing kernel at R rows per lane and ng pairs per wave; nullptr when
+// it is not compiled.
+void* grad_rev_fn(int lam, int R, int ng, int d, bool ys);
 bool grad_supported(int lam, int dim);
 
 // Point gradients of one batch from a gradient launch's increment gradients
