@@ -165,6 +165,71 @@ int64_t choose_sweep_run(int64_t nx, int64_t ny, int64_t cols, bool sym, int32_t
   return best;
 }
 
+// Rows per lane, runs per wave and pairs per run of a one-wave forward Gram
+// sweep (R = 0: none is compiled), by the least modelled time of the busiest
+// SIMD.  A wave streams its runs in (pairs n + lanes - 1) steps; a step issues
+// per lane about 0.64 d per coarse row (float32 FMAs, in units of a double
+// one), 2 per fine cell, 2 (implicit: 8) per coarse row, 2^(lam + 1) DPP moves
+// and 16 more.  The busiest SIMD holds ceil(waves / SIMDs) waves, of which as
+// many run at once as the registers allow; with one, two or three it issues at
+// 0.73, 0.93 or 0.97 of its rate with four or more.  run: the tuned value or
+// 0; ties go to the shorter run.  (Both sides measured: sweep_fwd_kernel.h.)
+struct SweepShape {
+  int R, ng;
+  int64_t run;
+};
+
+SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t n, int lam,
+                              int d, bool implicit, bool sym, bool no_diag, int32_t run) {
+  const int64_t simds = device_simds();
+  const int64_t M = fine_rows < 1 ? 1 : fine_rows;
+  const int64_t cap = ny < 64 ? (ny < 1 ? 1 : ny) : 64;
+  const int64_t tuned = run < ny ? run : (ny > 0 ? ny : 1);
+  const int64_t s = sym && no_diag ? 1 : 0;
+  const int dp = sk::padded_dim(d);
+  SweepShape best{0, 1, 1};
+  double best_cost = 0.0;
+  auto consider = [&](int R, int ng, int64_t k) {
+    const int gl = 64 / ng, S = 1 << lam, cr = R >= S ? R / S : 1;
+    const double step = cr * (0.64 * d + (implicit ? 8.0 : 2.0)) + 2.0 * R * S + 2.0 * S + 16.0;
+    const int regs = 2 * R + cr * d + 3 * dp + 4 * S + 30;
+    const int64_t resident = regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
+    const int64_t rpr = (ny + k - 1) / k;
+    const int64_t runs = sym ? sk::tri_runs(nx - s, rpr, k, s) : nx * rpr;
+    const int64_t waves = (runs + ng - 1) / ng;
+    const int64_t per_simd = (waves + simds - 1) / simds;
+    const int64_t at_once = per_simd < resident ? per_simd : resident;
+    const double rate = at_once >= 4 ? 1.0 : at_once == 3 ? 0.97 : at_once == 2 ? 0.93 : 0.73;
+    const double cost = (double)per_simd * (double)(k * n + gl - 1) * step / rate;
+    if (best.R == 0 || cost < best_cost) {
+      best = SweepShape{R, ng, k};
+      best_cost = cost;
+    }
+  };
+  const int64_t pairs = sym ? nx * (nx + 1) / 2 : nx * ny;
+  for (int ng : {1, 4}) {
+    const int64_t gl = 64 / ng;
+    for (int R : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
+      // more rows than the path's mean less fixed work per row: heights up to
+      // four times the least one
+      if (gl * R < M || gl * R >= 4 * M + 64) continue;
+      if (!sk::forward_fn(implicit, lam, R, ng, d)) continue;
+      // single pairs, and about four waves per SIMD
+      const int64_t k = pairs / (4 * simds * ng);
+      if (run > 0) {
+        consider(R, ng, tuned);
+      } else {
+        consider(R, ng, 1);
+        if (k > 1) consider(R, ng, k < cap ? k : cap);
+        if (k >= 1 && k < cap) consider(R, ng, k + 1);
+      }
+    }
+  }
+  if (run <= 0 && best.R > 0)
+    for (int64_t k = 1; k <= cap; ++k) consider(best.R, best.ng, k);
+  return best;
+}
+
 // Independent pairs: the forward layout (increments not scaled), the pair
 // plan (order, class counts, queue counters) and one band buffer per
 // persistent wave slot.
@@ -676,6 +741,7 @@ void set_triangle(sk::SweepArgs& a, int mode) {
   const int64_t s = a.no_diag ? 1 : 0;
   a.tri = (int32_t)(1 + s);
   a.n_waves = a.nx > s ? sk::tri_runs(a.nx - s, a.runs_per_row, a.run, s) : 0;
+  a.tri32 = (a.nx + 1) * a.runs_per_row <= INT32_MAX && (a.nx + 1) * a.run <= INT32_MAX ? 1 : 0;
 }
 
 sk_status zero_skipped_diagonal(const sk::SweepArgs& a, hipStream_t stream) {
@@ -698,8 +764,7 @@ sk_status run_forward(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32
   const int d = X->dim;
   const int dp = sk::padded_dim(d);
   const int64_t fine_rows = (int64_t)(Xr.len - 1) << lam;
-  const int R = sk::choose_rows_per_lane(fine_rows < 1 ? 1 : fine_rows, lam, d);
-  if (R == 0) {
+  if (!sk::forward_takes(fine_rows, lam, d)) {
     // x paths taller than one wave's strips: every (a, b) through the
     // persistent pair kernel with row bands (a symmetric Gram is filled in
     // both halves by solving both)
@@ -750,20 +815,16 @@ sk_status run_forward(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32
   a.implicit = implicit ? 1 : 0;
   a.out = out;
   a.out_ld = Y->n_paths;
-  if (mode == 0) {
-    a.run = 1;
-    a.runs_per_row = 1;
-    a.n_waves = X->n_paths;
-  } else {
-    a.run = Y->offsets ? 1
-                       : (int32_t)choose_sweep_run(X->n_paths, Y->n_paths,
-                                                   (int64_t)(Y->len - 1) << lam, mode == 2,
-                                                   tune.run, a.no_diag != 0);
-    a.runs_per_row = (Y->n_paths + a.run - 1) / a.run;
-    a.n_waves = X->n_paths * a.runs_per_row;
-    set_triangle(a, mode);
-  }
-  const hipError_t e = sk::launch_sweep(a, lam, R, d, stream, tune.waves_per_block);
+  const SweepShape sh =
+      choose_sweep_shape(X->n_paths, Y->n_paths, fine_rows, Yr.len - 1, lam, d, implicit,
+                         mode == 2, a.no_diag != 0, Y->offsets ? 1 : tune.run);
+  if (sh.R == 0) return SK_ERR_UNSUPPORTED;
+  a.run = (int32_t)sh.run;
+  a.runs_per_row = (Y->n_paths + a.run - 1) / a.run;
+  a.n_waves = X->n_paths * a.runs_per_row;
+  set_triangle(a, mode);
+  const hipError_t e =
+      sk::launch_sweep(a, lam, sh.R, sh.ng, d, stream, tune.waves_per_block);
   if (e == hipErrorInvalidValue) return SK_ERR_UNSUPPORTED;
   if (e != hipSuccess) return SK_ERR_HIP;
   return zero_skipped_diagonal(a, stream);

@@ -12,6 +12,15 @@ constexpr bool sweep_fits(int R, int LAM, int D) {
   return ((R >> LAM) > 0 ? (R >> LAM) : 1) * D <= 96 && R <= 32;
 }
 
+// The forward Gram sweep's rows per lane on 64 / ng lanes: whole coarse rows per
+// lane or whole lanes per coarse row, in steps of a quarter to a third so that
+// at least three quarters of the lanes' rows are real at most path lengths.
+constexpr bool forward_fits(int R, int LAM, int D, int ng) {
+  const int S = 1 << LAM;
+  if (!sweep_fits(R, LAM, D) || (R % S != 0 && S % R != 0)) return false;
+  return ng == 1 ? R >= 2 : (ng == 4 && R <= 16);
+}
+
 // Largest power-of-two rows per lane (at most 32) that sweep_fits allows.
 // The pipelined band kernel only runs when the tallest grid needs several
 // bands, which happens only at this height, so it is compiled at it alone.

@@ -50,34 +50,16 @@
 namespace sk {
 namespace grad {
 
+using fwd::group_prev;
+
 // Largest accepted difference between a rebuilt node and the forward one.
 constexpr double kRevTol = 1.0 / (1 << 28);
 __device__ __forceinline__ bool drifted(double rebuilt, double forward) {
   return !(fabs(rebuilt - forward) <= kRevTol * fmax(1.0, fabs(forward)));
 }
 
-// Lane l receives lane l-1's value within its group of 64 / NG lanes; a
-// group's first lane keeps `keep`.
-template <int NG>
-__device__ __forceinline__ double group_prev(double v, double keep, bool first) {
-  if constexpr (NG == 1) {
-    return from_prev_lane(v, keep);
-  } else if constexpr (NG == 4) {  // a row of 16 lanes: row_shr:1
-    const unsigned long long bv = (unsigned long long)__double_as_longlong(v);
-    const unsigned long long bk = (unsigned long long)__double_as_longlong(keep);
-    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)bk, (int)(unsigned)bv, 0x111, 0xF,
-                                               0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(bk >> 32),
-                                               (int)(unsigned)(bv >> 32), 0x111, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) |
-                                            (unsigned long long)(unsigned)lo));
-  } else {
-    const double t = from_prev_lane(v, keep);
-    return first ? keep : t;
-  }
-}
-
-// Lane l receives lane l+1's value within its group; the last lane keeps `keep`.
+// Lane l receives lane l+1's value within its group of 64 / NG lanes; a group's
+// last lane keeps `keep`.
 template <int NG, class T>
 __device__ __forceinline__ T group_next(T v, T keep, bool last) {
   if constexpr (NG == 1) {

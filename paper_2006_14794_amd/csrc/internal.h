@@ -70,12 +70,17 @@ namespace sk {
 // Largest number of fine rows per lane of the one-wave sweep.
 constexpr int kMaxRowsPerLane = 32;
 
-// Rows per lane for `fine_rows` rows on a 64-lane wave (0 if none is compiled).
-int choose_rows_per_lane(int64_t fine_rows, int lam, int dim);
+// The one-wave forward Gram sweep at R rows per lane and ng runs per wave;
+// nullptr when it is not compiled.
+void* forward_fn(bool implicit, int lam, int R, int ng, int dim);
+// Whether some compiled forward Gram sweep takes `fine_rows` rows (taller x
+// paths go through the persistent pair kernel in row bands).
+bool forward_takes(int64_t fine_rows, int lam, int dim);
 
-// Returns hipErrorInvalidValue when no compiled configuration covers the shape.
-// waves_per_block: 1, 2 or 4 one-wave sweeps per workgroup (0: 4).
-hipError_t launch_sweep(const SweepArgs& a, int lam, int rows_per_lane, int dim,
+// a.n_waves counts runs, ng of them per wave.  Returns hipErrorInvalidValue
+// when no compiled configuration covers the shape.  waves_per_block: 1, 2 or 4
+// waves per workgroup (0: 4).
+hipError_t launch_sweep(const SweepArgs& a, int lam, int rows_per_lane, int ng, int dim,
                         hipStream_t stream, int waves_per_block = 0);
 // The sweep of the Gaussian-lifted kernel (lifted_kernel.h): incx / incy hold
 // node rows, lift_inv and lift_scale are set.
@@ -262,10 +267,9 @@ hipError_t launch_gram_rows(const GramArgs& a, int precision, hipStream_t stream
 constexpr int kGramMfmaMaxDim = 64;
 hipError_t launch_gram_mfma(const GramArgs& a, int precision, hipStream_t stream);
 
-// Compiled sweep kernels by kind, dyadic order, rows per lane and channels
+// Compiled sweep kernels (beside forward_fn's) by kind, dyadic order, rows per lane and channels
 // (nullptr when the configuration is not compiled).
-enum { kKernelForward = 0, kKernelPair = 3, kKernelLifted = 4, kKernelForwardImplicit = 5,
-       kKernelPairBand = 6, kKernelPairBandFull = 7 };
+enum { kKernelPair = 3, kKernelLifted = 4, kKernelPairBand = 6, kKernelPairBandFull = 7 };
 void* sweep_fn(int kind, int lam, int rows_per_lane, int dim);
 
 }  // namespace sk

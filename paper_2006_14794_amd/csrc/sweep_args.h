@@ -28,6 +28,7 @@ struct SweepArgs {
   int64_t runs_per_row;     // ceil(ny / run)
   int32_t tri;       // mode 2: waves enumerate only the runs of the upper triangle
                      // (tri_runs): 1 with the diagonal, 2 without it
+  int32_t tri32;     // ... and nx runs_per_row < 2^31: 32-bit arithmetic serves
   int64_t n_waves;
   float* out;               // nullptr: terminal values not written
   int64_t out_ld;           // ny for the Gram
@@ -45,10 +46,10 @@ struct SweepArgs {
 // of three).
 constexpr int64_t kStreamPad = 128;
 
-// Steps of a wave that streams `total` coarse columns (a multiple of three:
-// the y-row prefetch rotates three buffers).
-__host__ __device__ inline int64_t sweep_steps(int64_t total) {
-  return ((total + 63 + 2) / 3) * 3;
+// Steps of a wavefront of `lanes` lanes that streams `total` coarse columns (a
+// multiple of three: the y-row prefetch rotates three buffers).
+__host__ __device__ inline int64_t sweep_steps(int64_t total, int lanes = 64) {
+  return ((total + lanes - 1 + 2) / 3) * 3;
 }
 
 // The upper triangle of a symmetric Gram by runs: row i (x_i) takes the y
@@ -59,10 +60,15 @@ __host__ __device__ inline int64_t sweep_steps(int64_t total) {
 // over these alone (no wave without a pair) are spread evenly over the
 // compute units; tri_runs(i) counts the runs of rows 0 .. i-1:
 //   i runs_per_row - sum_{j < i + s} floor(j / run).
+template <class I>
+__host__ __device__ inline I tri_runs_of(I i, I runs_per_row, I run, I s) {
+  const I x = i + s, q = x / run, r = x - q * run;
+  // (q (q - 1) is 0, not a wrapped product, at q = 0 for unsigned I)
+  return i * runs_per_row - (q ? run * (q * (q - 1) / 2) : 0) - q * r;
+}
 __host__ __device__ inline int64_t tri_runs(int64_t i, int64_t runs_per_row, int64_t run,
                                             int64_t s = 0) {
-  const int64_t x = i + s, q = x / run, r = x - q * run;
-  return i * runs_per_row - (run * q * (q - 1) / 2 + q * r);
+  return tri_runs_of<int64_t>(i, runs_per_row, run, s);
 }
 
 }  // namespace sk

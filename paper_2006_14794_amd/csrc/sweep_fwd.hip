@@ -1,33 +1,51 @@
 // Launchers of the forward sweep kernels (sweep_fwd_kernel.h) and the table of
 // compiled configurations (instantiated per dyadic order in sweep_lam*.hip).
+#include "dispatch.h"
 #include "internal.h"
 
 namespace sk {
 
 #define SK_DECL(k, l) void* sweep_fn_k##k##_l##l##_(int R, int d);
-SK_DECL(0, 0) SK_DECL(0, 1) SK_DECL(0, 2) SK_DECL(0, 3)
 SK_DECL(3, 0) SK_DECL(3, 1) SK_DECL(3, 2) SK_DECL(3, 3)
 SK_DECL(4, 0) SK_DECL(4, 1) SK_DECL(4, 2) SK_DECL(4, 3)
-SK_DECL(5, 0) SK_DECL(5, 1) SK_DECL(5, 2) SK_DECL(5, 3)
 SK_DECL(6, 0) SK_DECL(6, 1) SK_DECL(6, 2) SK_DECL(6, 3)
 SK_DECL(7, 0) SK_DECL(7, 1) SK_DECL(7, 2) SK_DECL(7, 3)
 #undef SK_DECL
+#define SK_DECL(k, l) void* sweep_fn_k##k##_l##l##_g1(int R, int d); void* sweep_fn_k##k##_l##l##_g4(int R, int d);
+SK_DECL(0, 0) SK_DECL(0, 1) SK_DECL(0, 2) SK_DECL(0, 3)
+SK_DECL(5, 0) SK_DECL(5, 1) SK_DECL(5, 2) SK_DECL(5, 3)
+#undef SK_DECL
 
-void* none_(int, int) { return nullptr; }  // kinds 1 and 2 are not compiled
+void* none_(int, int) { return nullptr; }  // kinds 1 and 2 are not compiled, 0 and 5 by forward_fn
 
 void* sweep_fn(int kind, int lam, int R, int d) {
   using Pick = void* (*)(int, int);
   static const Pick table[8][4] = {
-      {sweep_fn_k0_l0_, sweep_fn_k0_l1_, sweep_fn_k0_l2_, sweep_fn_k0_l3_},
+      {none_, none_, none_, none_},
       {none_, none_, none_, none_},
       {none_, none_, none_, none_},
       {sweep_fn_k3_l0_, sweep_fn_k3_l1_, sweep_fn_k3_l2_, sweep_fn_k3_l3_},
       {sweep_fn_k4_l0_, sweep_fn_k4_l1_, sweep_fn_k4_l2_, sweep_fn_k4_l3_},
-      {sweep_fn_k5_l0_, sweep_fn_k5_l1_, sweep_fn_k5_l2_, sweep_fn_k5_l3_},
+      {none_, none_, none_, none_},
       {sweep_fn_k6_l0_, sweep_fn_k6_l1_, sweep_fn_k6_l2_, sweep_fn_k6_l3_},
       {sweep_fn_k7_l0_, sweep_fn_k7_l1_, sweep_fn_k7_l2_, sweep_fn_k7_l3_}};
   if (kind < 0 || kind > 7 || lam < 0 || lam > 3) return nullptr;
   return table[kind][lam](R, d);
+}
+
+void* forward_fn(bool implicit, int lam, int R, int ng, int d) {
+  using Pick = void* (*)(int, int);
+#define SK_ROW(k, l) {sweep_fn_k##k##_l##l##_g1, sweep_fn_k##k##_l##l##_g4}
+  static const Pick table[2][4][2] = {{SK_ROW(0, 0), SK_ROW(0, 1), SK_ROW(0, 2), SK_ROW(0, 3)},
+                                      {SK_ROW(5, 0), SK_ROW(5, 1), SK_ROW(5, 2), SK_ROW(5, 3)}};
+#undef SK_ROW
+  if (lam < 0 || lam > 3 || (ng != 1 && ng != 4)) return nullptr;
+  return table[implicit ? 1 : 0][lam][ng == 1 ? 0 : 1](R, d);
+}
+
+bool forward_takes(int64_t fine_rows, int lam, int d) {
+  return lam >= 0 && lam <= 3 && d >= 1 && d <= 16 &&
+         fine_rows <= 64 * (int64_t)max_fitting_rows(lam, d);
 }
 
 int choose_rows_for(int kind, int64_t fine_rows, int lam, int d) {
@@ -38,32 +56,27 @@ int choose_rows_for(int kind, int64_t fine_rows, int lam, int d) {
   return 0;
 }
 
-int choose_rows_per_lane(int64_t fine_rows, int lam, int d) {
-  return choose_rows_for(kKernelForward, fine_rows, lam, d);
-}
-
 namespace {
-hipError_t launch_forward(int kind, const SweepArgs& a, int lam, int R, int d,
-                          hipStream_t stream, int wpb) {
-  auto f = reinterpret_cast<void (*)(const SweepArgs)>(sweep_fn(kind, lam, R, d));
+hipError_t launch_forward(void* fn, const SweepArgs& a, int ng, hipStream_t stream, int wpb) {
+  auto f = reinterpret_cast<void (*)(const SweepArgs)>(fn);
   if (!f) return hipErrorInvalidValue;
   if (a.n_waves == 0) return hipSuccess;
   if (wpb != 1 && wpb != 2) wpb = 4;  // the kernels are bounded to 256 threads
-  const int64_t blocks = (a.n_waves + wpb - 1) / wpb;
+  const int64_t blocks = (a.n_waves + wpb * ng - 1) / (wpb * ng);
   hipLaunchKernelGGL(f, dim3((unsigned)blocks), dim3(64 * wpb), 0, stream, a);
   return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_sweep(const SweepArgs& a, int lam, int R, int d, hipStream_t stream,
+hipError_t launch_sweep(const SweepArgs& a, int lam, int R, int ng, int d, hipStream_t stream,
                         int waves_per_block) {
-  return launch_forward(a.implicit ? kKernelForwardImplicit : kKernelForward, a, lam, R, d,
-                        stream, waves_per_block);
+  return launch_forward(forward_fn(a.implicit != 0, lam, R, ng, d), a, ng, stream,
+                        waves_per_block);
 }
 
 hipError_t launch_lifted(const SweepArgs& a, int lam, int R, int d, hipStream_t stream,
                          int waves_per_block) {
-  return launch_forward(kKernelLifted, a, lam, R, d, stream, waves_per_block);
+  return launch_forward(sweep_fn(kKernelLifted, lam, R, d), a, 1, stream, waves_per_block);
 }
 
 }  // namespace sk

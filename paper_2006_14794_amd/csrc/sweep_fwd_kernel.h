@@ -50,6 +50,27 @@ __device__ __forceinline__ double from_prev_lane(double v, double keep) {
                                           (unsigned long long)(unsigned)lo));
 }
 
+// The same within groups of 64 / NG lanes (NG 1, 2 or 4): a group's first lane
+// keeps `keep`.  A group of 16 lanes is a DPP row (row_shr:1); of two groups the
+// second one's first lane takes its own value back (`first`).
+template <int NG>
+__device__ __forceinline__ double group_prev(double v, double keep, bool first) {
+  static_assert(NG == 1 || NG == 2 || NG == 4, "groups of 64, 32 or 16 lanes");
+  if constexpr (NG == 4) {
+    const unsigned long long bv = (unsigned long long)__double_as_longlong(v);
+    const unsigned long long bk = (unsigned long long)__double_as_longlong(keep);
+    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)bk, (int)(unsigned)bv, 0x111, 0xF,
+                                               0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(bk >> 32),
+                                               (int)(unsigned)(bv >> 32), 0x111, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) |
+                                            (unsigned long long)(unsigned)lo));
+  } else {
+    const double t = from_prev_lane(v, keep);
+    return NG == 2 && first ? keep : t;
+  }
+}
+
 // The value of lane `l`, in scalar registers (uniform for the compiler).
 __device__ __forceinline__ double lane_value(double v, int l) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -134,16 +155,32 @@ __device__ __forceinline__ void store_out(const SweepArgs& a, int64_t ia, int64_
   }
 }
 
-// Resolves the run of pairs (x_ia, y_b), b in [b0, b1), of wave w, writes the
-// value of every pair with nothing to sweep (a broken path: NaN; a one-point
-// path: the boundary value 1; 0 on the diagonal of a symmetric Gram without
-// its diagonal, as for swept pairs), and returns false when the wave has no
-// columns to stream.  m: increments of x_ia; total: columns of the run.
-// Runs longer than one pair are only formed for uniform y batches, so every
-// pair of a run has the same width.
+// The last row of the upper triangle whose runs start at or before run w
+// (binary search on the increasing run counts).  I: 32-bit arithmetic where the
+// host found every count to fit (SweepArgs::tri32), which matters where the
+// lanes of a wave search for different runs: a 64-bit division there is about
+// a hundred vector instructions.
+template <class I>
+__device__ __forceinline__ I tri_row(const SweepArgs& a, I w, I s) {
+  I lo = 0, hi = (I)a.nx - s;
+  while (hi - lo > 1) {
+    const I mid = (lo + hi) >> 1;
+    if (tri_runs_of<I>(mid, (I)a.runs_per_row, (I)a.run, s) <= w) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// Resolves the run of pairs (x_ia, y_b), b in [b0, b1), of run w, swept by
+// `lanes` lanes of which this is lane `lane`; writes the value of every pair
+// with nothing to sweep (a broken path: NaN; a one-point path: the boundary
+// value 1; 0 on the diagonal of a symmetric Gram without its diagonal, as for
+// swept pairs), and returns false when there are no columns to stream.  m:
+// increments of x_ia; total: columns of the run.  Runs longer than one pair
+// are only formed for uniform y batches, so every pair of a run has the same
+// width.
 __device__ __forceinline__ bool wave_run(const SweepArgs& a, int64_t w, int lane, int rows,
                                          int lam, int64_t& ia, int64_t& b0, int64_t& b1,
-                                         int32_t& m, int64_t& total) {
+                                         int32_t& m, int64_t& total, int lanes = 64) {
   if (a.mode == 0) {
     ia = w;
     b0 = w;
@@ -151,16 +188,17 @@ __device__ __forceinline__ bool wave_run(const SweepArgs& a, int64_t w, int lane
   } else if (a.tri) {
     // s = 1: the triangle without its diagonal (the host zeroes it)
     const int64_t s = a.tri - 1;
-    // the last row whose runs start at or before wave w (binary search on
-    // the increasing run counts; the values are uniform over the wave)
-    int64_t lo = 0, hi = a.nx - s;
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (tri_runs(mid, a.runs_per_row, a.run, s) <= w) lo = mid; else hi = mid;
+    int64_t start;
+    if (a.tri32) {
+      const uint32_t w32 = (uint32_t)w, s32 = (uint32_t)s, run = (uint32_t)a.run;
+      const uint32_t row = tri_row<uint32_t>(a, w32, s32);
+      ia = row;
+      start = ((row + s32) / run +
+               (w32 - tri_runs_of<uint32_t>(row, (uint32_t)a.runs_per_row, run, s32))) * run;
+    } else {
+      ia = tri_row<int64_t>(a, w, s);
+      start = ((ia + s) / a.run + (w - tri_runs(ia, a.runs_per_row, a.run, s))) * a.run;
     }
-    ia = lo;
-    const int64_t start =
-        ((ia + s) / a.run + (w - tri_runs(ia, a.runs_per_row, a.run, s))) * a.run;
     b0 = start > ia + s ? start : ia + s;  // the row's first run begins at column ia + s
     b1 = start + a.run < a.ny ? start + a.run : a.ny;
   } else {
@@ -190,7 +228,7 @@ __device__ __forceinline__ bool wave_run(const SweepArgs& a, int64_t w, int lane
   }
   if (m <= 0 || total == 0) return false;
   if (((int64_t)m << lam) > rows) {  // excluded by the host; never read past the lane rows
-    for (int64_t b = b0 + lane; b < b1; b += 64) store_out(a, ia, b, __builtin_nanf(""));
+    for (int64_t b = b0 + lane; b < b1; b += lanes) store_out(a, ia, b, __builtin_nanf(""));
     return false;
   }
   return true;
@@ -233,25 +271,43 @@ __device__ __forceinline__ void cell_block(double (&v)[R][1 << LAM],
 
 // IMPL: the implicit scheme's cell factor (a separate instantiation, so that
 // the explicit kernel carries none of its registers).
-template <int R, int LAM, int D, bool IMPL>
+//
+// NG > 1: short x paths.  A wave sweeps NG runs side by side, each on
+// GL = 64 / NG lanes of R rows: on 64 lanes a path of 88 fine rows takes two
+// rows per lane, and a step's instructions that do not grow with the rows (the
+// DPP moves, the y row, the bookkeeping: about 16) then serve four fine cells at
+// order 1 instead of 24 for six rows on each of 16 lanes; the wavefront's fill
+// is 15 steps instead of 63.  A group's lanes leave the kernel or its loop
+// together; no value crosses groups.  Bound: instruction issue.  Measured (call
+// times; before: powers of two rows on 64 lanes): symmetric Gram of 300 paths
+// of 45 points, d = 4, order 1, 65 us against 132; 256 x 256 of 20 points,
+// d = 3, order 0, 34 against 105, of 50 points, d = 5, 89 against 288.  With 3, 5,
+// 6, 10, 12, 20 and 24 rows per lane beside the powers of two: 100 x 100 of 300
+// points, d = 6, order 1 (598 rows on 64 x 10 instead of 64 x 16), 541 against
+// 833; 64 x 64 of 350 points, d = 12, order 2, 809 against 1118.
+template <int R, int LAM, int D, bool IMPL, int NG>
 __global__ __launch_bounds__(256) void sweep_kernel(const SweepArgs a) {
+  constexpr int GL = 64 / NG;
   constexpr int DP = (D + 3) & ~3;
   constexpr int S = 1 << LAM;                          // fine columns per coarse column
   constexpr int CR = (R >> LAM) > 0 ? (R >> LAM) : 1;  // coarse rows per lane
 
-  const int lane = threadIdx.x & 63;
-  const int64_t w = a.wave0 + (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (w >= a.wave0 + a.n_waves) return;  // uniform per wave
+  const int lane = threadIdx.x & (GL - 1);  // of the group
+  // the group's run (one run per wave: a scalar, and with it all of its prologue)
+  const int gid = NG == 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))
+                          : (int)(threadIdx.x / GL);
+  const int64_t w = a.wave0 + (int64_t)blockIdx.x * (blockDim.x / GL) + gid;
+  if (w >= a.wave0 + a.n_waves) return;  // uniform per group
 
   int64_t ia, b0, b1, total;
   int32_t m;
-  if (!wave_run(a, w, lane, 64 * R, LAM, ia, b0, b1, m, total)) return;
+  if (!wave_run(a, w, lane, GL * R, LAM, ia, b0, b1, m, total, GL)) return;
   const int M = m << LAM;
 
   // Lane strips are aligned to the bottom of the grid: cell row M - 1 is the
-  // last row of lane 63, and the rows above row 0 that the top strip covers
+  // last row of the last lane, and the rows above row 0 that the top strip covers
   // are virtual (zero increments, values identically 1 -- the boundary row).
-  const int row0 = lane * R - (64 * R - M);
+  const int row0 = lane * R - (GL * R - M);
   const int p0 = row0 >> LAM;  // floor division; negative for virtual rows
   const int64_t xrow = first_row(a.x_start, a.x_len, ia);
   float dx[CR][D];
@@ -295,7 +351,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(const SweepArgs a) {
   load_row<DP>(yp, dyA);
   load_row<DP>(yp + DP, dyB);
   // a multiple of 3 steps; the extra steps are inactive for every lane
-  const int32_t nsteps = (int32_t)sweep_steps(total);
+  const int32_t nsteps = (int32_t)sweep_steps(total, GL);
 
   // Three y-row buffers: step t reads buffer t % 3 and refills buffer
   // (t + 2) % 3, which step t - 1 has finished with, so the two-step-ahead
@@ -312,7 +368,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(const SweepArgs a) {
     }
 
 #pragma unroll
-    for (int cc = 0; cc < S; ++cc) up[cc] = from_prev_lane(pub[cc], up[cc]);
+    for (int cc = 0; cc < S; ++cc) up[cc] = group_prev<NG>(pub[cc], up[cc], lane == 0);
 
     if ((uint32_t)g < (uint32_t)total32) {
       double gk[CR];
@@ -336,7 +392,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(const SweepArgs a) {
       if (++q == cn) {
         // last column of a pair: emit its terminal value, then the left
         // boundary (value 1) of the next pair of the run
-        if (lane == 63) {
+        if (lane == GL - 1) {
           const int64_t cb = b0 + g / cn;
           store_out(a, ia, cb, (a.mode == 2 && a.no_diag && cb == ia) ? 0.0f : (float)u[R - 1]);
         }

@@ -48,7 +48,7 @@ std::vector<sk_tune> candidates(int32_t op, const sk_paths* X, const sk_paths* Y
   // the same fine rows
   const int64_t fine_rows = (int64_t)(X->len > 1 ? X->len - 1 : 1) << lam;
   const bool pair_path = op == SK_OP_PAIR ||
-                         sk::choose_rows_per_lane(fine_rows, lam > 3 ? 3 : lam, X->dim) == 0;
+                         !sk::forward_takes(fine_rows, lam > 3 ? 3 : lam, X->dim);
   if (pair_path) {
     for (int b : {0, 1, 2, 3, 4, 6, 8}) c.push_back(sk_tune{0, 0, b, 0});
     for (int b : {0, 2, 4}) c.push_back(sk_tune{0, 0, b, 1});  // sequential bands
