@@ -244,6 +244,7 @@ constexpr size_t kPipeCapBytes = size_t(1) << 30;
 constexpr int64_t kSimds = 1024;
 
 struct PairLayout {
+  Order o;                     // kernel order and refinement
   int rows_lo, rows_hi;
   int64_t slots, band_stride;  // doubles per slot
   bool pipe;                   // long class as pipelined band tasks
@@ -251,15 +252,97 @@ struct PairLayout {
   size_t order, counts, bands, task_base, tbuf, total;
 };
 
-PairLayout pair_layout(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, bool gram) {
-  const Order o = split_order(lam0);
-  const sk_paths Xr = refined(X0, o.rep), Yr = refined(Y0, o.rep);
+// Kernel order and band height of a uniform batch of few long pairs: the order
+// lam0 may run as any kernel order k <= min(lam0, 3) on increments split into
+// 2^(lam0 - k) parts (the same fine cells and coefficients, bit for bit), and a
+// pair's rows as bands of 64 R.  A pair's bands form a chain, each lagging the
+// one above by a pipeline fill, the chunks in flight and the hand-over's
+// latency, about 100 steps, so it takes columns + 63 + 100 (bands - 1) steps.
+// A step of a wave alone on its SIMD takes about 8.8 cycles per fine cell,
+// 2.8 per float32 product and 350 + 20 2^k of latencies (its first and last
+// antidiagonals, the DPP hand-off, LDS) that shrink with neither R nor k:
+// small blocks pay them too often, large ones make every band of the chain
+// wait longer.  With more waves than SIMDs the chip's issue rate bounds the
+// time instead (200 cycles of other instructions per step).  Fitted to five
+// pairs of 2000 points, d = 2, order 4, measured at k = 1, 2, 3 with R = 4, 8,
+// 16: 5.24, 4.88, 5.88; 4.48, 3.88, 4.58; 5.75, 4.55, 5.18 ms.  (At k = 3 alone
+// and R = 16, with the memory operations in every step: 7.2 ms; the whole call
+// now 3.64.)  Three pairs of 1000 points, order 1: 305 us against 637 as one
+// wave each; 200 of 500 points, order 2: 252 against 501; 2000 of them keep one
+// wave per pair (806).
+struct BandChoice {
+  int k, R;  // R = 0: none
+  double cycles;
+};
+
+BandChoice choose_bands(const sk_paths* X, const sk_paths* Y, int32_t lam0, int64_t npairs,
+                        size_t inc_budget) {
+  BandChoice best{0, 0, 0.0};
+  const int64_t mx = X->len - 1, my = Y->len - 1;
+  const int64_t rows = (mx < my ? mx : my) << lam0;
+  const int d = X->dim;
+  for (int k = lam0 < kMaxKernelOrder ? lam0 : kMaxKernelOrder; k >= 0; --k) {
+    const int64_t rep = int64_t(1) << (lam0 - k), S = int64_t(1) << k;
+    const int64_t cols = (mx > my ? mx : my) * rep;
+    const size_t inc = ((size_t)X->n_paths * mx + (size_t)Y->n_paths * my) * (size_t)rep *
+                       (size_t)sk::padded_dim(d) * sizeof(float);
+    if (k < kMaxKernelOrder && k < lam0 && inc > inc_budget) break;
+    for (int R = 1; R <= sk::kMaxRowsPerLane; R *= 2) {
+      if (!sk::sweep_fn(sk::kKernelPairBandFull, k, R, d)) continue;
+      const int64_t nb = (rows + 64 * (int64_t)R - 1) / (64 * (int64_t)R);
+      const int64_t stride = (cols + 1 + 2 * sk::kStreamPad) << k;
+      if (nb < 2 || nb * npairs > INT32_MAX ||
+          (size_t)(nb * npairs) * (size_t)stride * sizeof(double) > kPipeCapBytes)
+        continue;
+      const double cell = 8.8 * (double)(R * S) + 2.8 * d * (double)(R >= S ? R / S : 1);
+      const double chain =
+          (double)(cols + 63 + (nb - 1) * 100) * (cell + 350.0 + 20.0 * (double)S);
+      const double issue = (double)(nb * npairs) * (double)(cols + 63) * (cell + 200.0) / kSimds;
+      const double cycles = chain > issue ? chain : issue;
+      if (best.R == 0 || cycles < best.cycles) best = BandChoice{k, R, cycles};
+    }
+  }
+  return best;
+}
+// Increments of a refined batch that the choice above may add to a workspace.
+constexpr size_t kBandIncBytes = size_t(64) << 20;
+
+// fixed_order: the caller launches the pair kernel itself, at order lam0.
+PairLayout pair_layout(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, bool gram,
+                       bool fixed_order = false) {
+  PairLayout L{};
+  L.o = split_order(lam0);
+  const int64_t npairs = gram ? X0->n_paths * Y0->n_paths : X0->n_paths;
+  const int d = X0->dim;
+  int force_rows = 0;
+  const int64_t least = (X0->len < Y0->len ? X0->len : Y0->len) - 1;
+  if (!fixed_order && !X0->offsets && !Y0->offsets && least << lam0 > 64) {
+    // against one wave per pair: its rows in one band of pair_kernel (about 600
+    // cycles of latencies a step) and some 15 us less for the launches
+    const int64_t longer = (X0->len > Y0->len ? X0->len : Y0->len) - 1;
+    const int64_t fine = least << lam0;
+    int R = 1;
+    while (R < sk::kMaxRowsPerLane && 64 * (int64_t)R < fine) R *= 2;
+    const bool one_band = 64 * (int64_t)R >= fine && sk::sweep_fn(sk::kKernelPair, L.o.k, R, d);
+    const BandChoice c = choose_bands(X0, Y0, lam0, npairs, kBandIncBytes);
+    double single = 0.0;
+    if (one_band) {
+      const double cell = 8.8 * (double)(R << L.o.k) +
+                          2.8 * d * (double)((R >> L.o.k) > 0 ? R >> L.o.k : 1);
+      const double steps = (double)(longer * L.o.rep + 63);
+      const double chain = steps * (cell + 600.0);
+      const double issue = (double)npairs * steps * (cell + 200.0) / kSimds;
+      single = (chain > issue ? chain : issue) * 0.9;
+    }
+    if (c.R > 0 && (!one_band || c.cycles + 36e3 < single)) {
+      L.o = Order{c.k, 1 << (lam0 - c.k)};
+      force_rows = c.R;
+    }
+  }
+  const sk_paths Xr = refined(X0, L.o.rep), Yr = refined(Y0, L.o.rep);
   const sk_paths* X = &Xr;
   const sk_paths* Y = &Yr;
-  const int32_t lam = o.k;
-  PairLayout L{};
-  const int64_t npairs = gram ? X->n_paths * Y->n_paths : X->n_paths;
-  const int d = X->dim;
+  const int32_t lam = L.o.k;
   // rows of the longest possible pair (its shorter path on the rows)
   const int64_t shorter = (X->len < Y->len ? X->len : Y->len) - 1;
   const int64_t rows = (shorter < 1 ? 1 : shorter) << lam;
@@ -268,39 +351,7 @@ PairLayout pair_layout(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, boo
     if (sk::sweep_fn(sk::kKernelPair, lam, R, d)) rmax = R;
   int rhi = 1;
   while (rhi < rmax && 64 * (int64_t)rhi < rows) rhi *= 2;
-  // Few long pairs of equal length: lower bands (fewer rows per lane) keep
-  // more SIMDs busy and make each step cheaper, at the price of more
-  // hand-overs, each band lagging the one above by about a pipeline fill plus
-  // a staging chunk (80 steps).  Modelled time of a pair: (columns + 63 +
-  // (bands - 1) 80) steps of cost R + 20, times the waves per SIMD beyond one.
-  // The 20 rows stand for the part of a step that does not shrink with R: a
-  // wave alone on its SIMD waits on latencies (DPP hand-off, loads, the
-  // cells' dependency chain) more than it issues.  Fitted to five pairs of
-  // 2000 points at order 4 (8.05, 6.98, 7.60, 10.77 ms at R = 32, 16, 8, 4).
-  if (rmax && rhi == rmax && !X0->offsets && !Y0->offsets && rows > 64 * (int64_t)rmax) {
-    const int64_t cols = (X->len > Y->len ? X->len : Y->len) - 1;
-    auto cost = [&](int R) {
-      const int64_t nb = (rows + 64 * (int64_t)R - 1) / (64 * (int64_t)R);
-      const double share = (double)(nb * npairs) / kSimds;
-      return (double)(cols + 63 + (nb - 1) * 80) * (R + 20) * (share > 1.0 ? share : 1.0);
-    };
-    // a height whose band tasks' slot buffers exceed the budget would lose
-    // the pipeline: not a candidate
-    const int64_t stride = (X->len > Y->len ? X->len : Y->len) + 2 * sk::kStreamPad;
-    auto fits = [&](int R) {
-      const int64_t nb = (rows + 64 * (int64_t)R - 1) / (64 * (int64_t)R);
-      return (size_t)(nb * npairs) * (size_t)(stride << lam) * sizeof(double) <= kPipeCapBytes;
-    };
-    double best = cost(rmax);
-    for (int R = rmax / 2; R >= 1; R /= 2) {
-      if (!sk::sweep_fn(sk::kKernelPairBandFull, lam, R, d) || !fits(R)) continue;
-      const double c = cost(R);
-      if (c < best) {
-        best = c;
-        rhi = R;
-      }
-    }
-  }
+  if (force_rows) rhi = force_rows;
   L.rows_hi = rmax ? rhi : 0;
   L.rows_lo = rhi > 1 ? rhi / 2 : rhi;
   // wave slots: a whole number of 4-wave workgroups
@@ -538,7 +589,7 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   if (npairs > INT32_MAX) return SK_ERR_UNSUPPORTED;
   if (PL.rows_hi == 0) return SK_ERR_UNSUPPORTED;
   if (ws_bytes < PL.total) return SK_ERR_WORKSPACE;
-  const Order o = split_order(lam0);
+  const Order o = PL.o;
   const int32_t lam = o.k;
   const sk_paths Xr = refined(X, o.rep), Yr = refined(Y, o.rep);
   const ForwardLayout L = forward_layout(&Xr, &Yr);
@@ -914,7 +965,7 @@ struct PredictLayout {
 
 PredictLayout predict_layout(const sk_paths* X, const sk_paths* Y, int32_t lam) {
   PredictLayout L{};
-  L.pl = pair_layout(X, Y, lam, false);
+  L.pl = pair_layout(X, Y, lam, false, true);
   const size_t n = (size_t)X->n_paths;
   size_t off = L.pl.total;
   L.wb = off;

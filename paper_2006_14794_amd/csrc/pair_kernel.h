@@ -14,6 +14,8 @@
 #pragma once
 #include <math.h>
 
+#include <type_traits>
+
 #include "internal.h"
 #include "sweep_fwd_kernel.h"
 
@@ -208,30 +210,60 @@ __global__ __launch_bounds__(256) void pair_kernel(const PairArgs a) {
 //     wave is running, so the chain always advances; the wait is bounded all
 //     the same, and on expiry the missing values become NaN, which flows to
 //     the pair's output and releases the bands below.
-constexpr int kChunk = 16;         // coarse columns staged per chunk
+constexpr int kChunk = 16;          // coarse columns staged per chunk
 constexpr int kSpinMax = 1 << 18;  // polls per value before giving up
+constexpr int kYRing = 128;        // y rows held in LDS: at least 64 + kChunk, a power of two
 
 __device__ __forceinline__ bool is_sentinel(double v) {
   return (uint64_t)__double_as_longlong(v) == kBandSlotSentinel;
 }
 
+// LDS of one wave of the pipelined band kernel.
+template <int LAM, int D>
+struct BandStage {
+  static constexpr int DP = (D + 3) & ~3;
+  // floats per y row: 16-byte reads of consecutive rows by consecutive lanes
+  // then touch every bank
+  static constexpr int YS = DP == 4 ? 4 : DP + 4;
+  float y[kYRing * YS];            // y rows, by column mod kYRing
+  double up[2][kChunk << LAM];     // upper neighbours of lane 0, two chunks
+  double low[kChunk << LAM];       // lane 63's bottom row, by column mod kChunk
+};
+
 // One band task: the band's lanes hold RT fine rows each, lane l's first row
 // being row0 (rows above row 0 are virtual: zero increments, value 1).  top:
 // the band's upper neighbours are the boundary; last: it ends the pair and
 // lane 63 writes the pair's value.
-template <int RT, int LAM, int D>
-__device__ __forceinline__ void band_sweep(const PairArgs& a,
-                                           double (&stage)[2][kChunk << LAM], int lane,
+//
+// A few long pairs leave each wave alone on its SIMD, and then a step costs
+// its latencies.  A step that loads a y row and stores lane 63's bottom row
+// waits, every step, for memory operations issued two steps earlier (on gfx950
+// loads and stores share one counter, and the stores are acknowledged across
+// the XCDs): about 1000 cycles a step whatever the rows.  So every memory
+// operation happens once per chunk of kChunk steps, a whole chunk ahead of its
+// use: the chunk's y rows, the upper neighbours and the bottom row pass through
+// LDS, and a step reads LDS one step ahead.  Five pairs of 2000 points, d = 2,
+// order 4 (32 000 x 32 000 fine cells each): see pair_layout's model.
+//
+// LONE: step loops of their own for either scheme and for the steps in which
+// every lane is inside the pair's columns, so that a step has no branch but
+// lane 63's store: alone on its SIMD a wave pays each taken branch in full
+// (3.88 ms against 4.63 on the five pairs above).  With several waves per SIMD
+// and three band heights in one kernel the extra bodies cost more than they
+// save (4096 ragged pairs: 3.30 ms against 2.90), so the fitted kernel has one.
+template <int RT, int LAM, int D, bool LONE>
+__device__ __forceinline__ void band_sweep(const PairArgs& a, BandStage<LAM, D>& st, int lane,
                                            int32_t tau, bool top, bool last, int row0,
                                            int32_t pid, int32_t m, int32_t n,
                                            const float* __restrict__ rinc,
                                            const float* __restrict__ cinc) {
   constexpr int DP = (D + 3) & ~3;
+  constexpr int YS = BandStage<LAM, D>::YS;
   constexpr int S = 1 << LAM;
   constexpr int CR = (RT >> LAM) > 0 ? (RT >> LAM) : 1;
   constexpr int CHS = kChunk * S;        // doubles per chunk
   constexpr int PER = (CHS + 63) / 64;   // doubles per lane per chunk
-  const int32_t nsteps = (int32_t)sweep_steps(n);
+  static_assert(kChunk * DP / 4 <= 64 && kYRing >= 64 + kChunk, "one float4 per lane and chunk");
   double* __restrict__ own = a.tbuf + (int64_t)tau * a.tstride;
   const double* __restrict__ above = a.tbuf + (int64_t)(tau - 1) * a.tstride;
 
@@ -250,10 +282,16 @@ __device__ __forceinline__ void band_sweep(const PairArgs& a,
     for (int q = 0; q < D; ++q) dx[c][q] = t[q];
   }
 
-  // upper neighbours of lane 0, staged chunk by chunk from the band above
+  // a chunk's y rows and upper neighbours of lane 0, in registers until the
+  // chunk begins
   bool failed = false;  // wave-uniform
   double pf[PER];
+  float4 py;
   auto fetch = [&](int32_t chunk) {  // issue the loads of a chunk
+    py = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int32_t yc = chunk * kChunk + lane / (DP / 4);
+    if (lane < kChunk * (DP / 4) && yc < n)
+      py = reinterpret_cast<const float4*>(cinc)[(int64_t)yc * (DP / 4) + lane % (DP / 4)];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = lane + 64 * i;
@@ -265,6 +303,10 @@ __device__ __forceinline__ void band_sweep(const PairArgs& a,
     }
   };
   auto commit = [&](int32_t chunk) {  // wait for a chunk's values, then stage them
+    if (lane < kChunk * (DP / 4))
+      *reinterpret_cast<float4*>(
+          &st.y[((chunk * kChunk + lane / (DP / 4)) & (kYRing - 1)) * YS + 4 * (lane % (DP / 4))]) =
+          py;
     bool missing = false;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -284,10 +326,21 @@ __device__ __forceinline__ void band_sweep(const PairArgs& a,
           missing = true;
         }
       }
-      if (e < CHS) stage[chunk & 1][e] = top ? 1.0 : v;
+      if (e < CHS) st.up[chunk & 1][e] = top ? 1.0 : v;
     }
     // a value that never came poisons the rest of this band (no more waits)
     failed = failed || __ballot(missing) != 0;
+  };
+  auto flush = [&](int32_t c0) {  // the bottom row at columns c0 .. c0 + kChunk - 1
+    if (last) return;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = lane + 64 * i;
+      const int32_t col = c0 + e / S;
+      if (e < CHS && (uint32_t)col < (uint32_t)n)
+        __hip_atomic_store(own + (int64_t)col * S + (e % S), st.low[e], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
   };
 
   double u[RT];
@@ -297,48 +350,43 @@ __device__ __forceinline__ void band_sweep(const PairArgs& a,
 #pragma unroll
   for (int cc = 0; cc < S; ++cc) pub[cc] = 1.0;
   double up_last = 1.0;
-  int32_t g = -lane;
-  const float* __restrict__ yp = cinc + (int64_t)g * DP;
-  auto bnd_load = [&](int32_t t, double (&v)[S]) {
-#pragma unroll
-    for (int cc = 0; cc < S; ++cc) v[cc] = stage[(t / kChunk) & 1][(t % kChunk) * S + cc];
+  struct In {
+    float dy[DP];
+    double up[S];
   };
-
-  fetch(0);
-  commit(0);
-  fetch(1);
-  float dyA[DP], dyB[DP], dyC[DP];
-  double bA[S], bB[S], bC[S];
-  load_row<DP>(yp, dyA);
-  load_row<DP>(yp + DP, dyB);
-  bnd_load(0, bA);
-  bnd_load(1, bB);
-  double result = 1.0;
-
-  auto step = [&](int32_t t, float (&dy)[DP], float (&refill)[DP], double (&bv)[S],
-                  double (&brefill)[S]) {
-    load_row<DP>(yp + 2 * DP, refill);
-    if ((t + 2) % kChunk == 0) {  // the next chunk is read from step t on
-      const int32_t c = (t + 2) / kChunk;
-      commit(c);
-      fetch(c + 1);
+  auto read_in = [&](int32_t t, In& in) {  // inputs of step t (t >= 0)
+    const float4* r = reinterpret_cast<const float4*>(&st.y[((t - lane) & (kYRing - 1)) * YS]);
+#pragma unroll
+    for (int c = 0; c < DP / 4; ++c) {
+      const float4 f = r[c];
+      in.dy[4 * c + 0] = f.x;
+      in.dy[4 * c + 1] = f.y;
+      in.dy[4 * c + 2] = f.z;
+      in.dy[4 * c + 3] = f.w;
     }
-    bnd_load(t + 2, brefill);
+#pragma unroll
+    for (int cc = 0; cc < S; ++cc) in.up[cc] = st.up[(t / kChunk) & 1][(t % kChunk) * S + cc];
+  };
+  // impl: 1 the implicit scheme's cell factor, 0 the explicit one, -1 as
+  // a.implicit says.  full: every lane is inside the pair's columns.
+  auto step = [&](auto impl, auto full, int32_t t, const In& in) {
+    constexpr int kImpl = decltype(impl)::value;
+    const int32_t g = t - lane;
     float h32[CR];
 #pragma unroll
     for (int c = 0; c < CR; ++c) {
       float s = 0.0f;
 #pragma unroll
-      for (int q = 0; q < D; ++q) s = __builtin_fmaf(dx[c][q], dy[q], s);
+      for (int q = 0; q < D; ++q) s = __builtin_fmaf(dx[c][q], in.dy[q], s);
       h32[c] = s;
     }
     double up[S];
 #pragma unroll
-    for (int cc = 0; cc < S; ++cc) up[cc] = from_prev_lane(pub[cc], bv[cc]);
+    for (int cc = 0; cc < S; ++cc) up[cc] = from_prev_lane(pub[cc], in.up[cc]);
 
-    if ((uint32_t)g < (uint32_t)n) {
+    if (decltype(full)::value || (uint32_t)g < (uint32_t)n) {
       double gk[CR];
-      if (a.implicit) {
+      if (kImpl == 1 || (kImpl < 0 && a.implicit)) {
         double h[CR];
 #pragma unroll
         for (int c = 0; c < CR; ++c) h[c] = (double)h32[c] * a.scale;  // exact: 2^-k
@@ -356,27 +404,52 @@ __device__ __forceinline__ void band_sweep(const PairArgs& a,
       for (int cc = 0; cc < S; ++cc) pub[cc] = v[RT - 1][cc];
       up_last = up[S - 1];
       if (lane == 63) {
-        if (!last) {
 #pragma unroll
-          for (int cc = 0; cc < S; ++cc)
-            __hip_atomic_store(own + (int64_t)g * S + cc, pub[cc], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        } else if (g == n - 1) {
-          result = u[RT - 1];
-        }
+        for (int cc = 0; cc < S; ++cc) st.low[(g & (kChunk - 1)) * S + cc] = pub[cc];
       }
     }
-    ++g;
-    yp += DP;
   };
 
-  for (int32_t t = 0; t < nsteps; t += 3) {
-    step(t, dyA, dyC, bA, bC);
-    step(t + 1, dyB, dyA, bB, bA);
-    step(t + 2, dyC, dyB, bC, bB);
+  // Iteration k runs the steps kChunk k - 1 .. kChunk (k + 1) - 2, so that the
+  // last column of a chunk of lane 63's bottom row (63 steps behind) ends with
+  // an iteration.
+  constexpr int kLag = 64 / kChunk + 1;  // chunks lane 63 is behind
+  const int32_t iters = (n + 63) / kChunk + 1;
+  fetch(0);
+  In ia, ib;
+#pragma unroll
+  for (int q = 0; q < DP; ++q) ia.dy[q] = 0.0f;
+#pragma unroll
+  for (int cc = 0; cc < S; ++cc) ia.up[cc] = 1.0;  // step -1: no lane is active
+  auto steps = [&](auto impl, auto full, int32_t t0) {
+#pragma unroll 1
+    for (int32_t j = 0; j < kChunk; j += 2) {
+      read_in(t0 + j + 1, ib);
+      step(impl, full, t0 + j, ia);
+      // (the read past the iteration's last step is its successor's first, in
+      // this chunk)
+      read_in(t0 + j + 2, ia);
+      step(impl, full, t0 + j + 1, ib);
+    }
+  };
+  for (int32_t k = 0; k < iters; ++k) {
+    commit(k);
+    flush(kChunk * (k - kLag));  // stores and loads stay in flight for the whole iteration
+    fetch(k + 1);
+    const int32_t t0 = kChunk * k - 1;
+    if constexpr (!LONE)
+      steps(std::integral_constant<int, -1>{}, std::false_type{}, t0);
+    else if (a.implicit)
+      steps(std::integral_constant<int, 1>{}, std::false_type{}, t0);
+    else if (t0 >= 63 && t0 + kChunk <= n)
+      steps(std::integral_constant<int, 0>{}, std::true_type{}, t0);
+    else
+      steps(std::integral_constant<int, 0>{}, std::false_type{}, t0);
   }
-  // lane 63 holds the value; every lane stores it (see pair_kernel)
-  result = fwd::lane_value(result, 63);
+  flush(kChunk * (iters - kLag));
+  // lane 63 holds the value (its rows keep it after the last column); every
+  // lane stores it (see pair_kernel)
+  const double result = fwd::lane_value(u[RT - 1], 63);
   if (last) a.out[pid] = (float)result;
 }
 
@@ -391,7 +464,7 @@ __device__ __forceinline__ void band_sweep(const PairArgs& a,
 template <int R, int LAM, int D, bool FIT_TOP>
 __global__ __launch_bounds__(256) void pair_band_kernel(const PairArgs a) {
   constexpr int DP = (D + 3) & ~3;
-  __shared__ double stage[4][2][kChunk << LAM];
+  __shared__ BandStage<LAM, D> stage[4];
 
   const int lane = threadIdx.x & 63;
   const int wl = threadIdx.x >> 6;
@@ -442,14 +515,14 @@ __global__ __launch_bounds__(256) void pair_band_kernel(const PairArgs a) {
     if (rt == R) {
       const int row0 = band > 0 ? top_rows + ((band - 1) * 64 + lane) * R
                                 : lane * R - (64 * R - top_rows);
-      band_sweep<R, LAM, D>(a, stage[wl], lane, tau, band == 0, last, row0, pid, m, n, rinc,
+      band_sweep<R, LAM, D, !FIT_TOP>(a, stage[wl], lane, tau, band == 0, last, row0, pid, m, n, rinc,
                             cinc);
     } else if (rt == half) {
-      band_sweep<(R >= 2 ? R / 2 : R), LAM, D>(a, stage[wl], lane, tau, true, last,
+      band_sweep<(R >= 2 ? R / 2 : R), LAM, D, !FIT_TOP>(a, stage[wl], lane, tau, true, last,
                                                lane * half - (64 * half - top_rows), pid, m,
                                                n, rinc, cinc);
     } else {
-      band_sweep<(R >= 4 ? R / 4 : R), LAM, D>(a, stage[wl], lane, tau, true, last,
+      band_sweep<(R >= 4 ? R / 4 : R), LAM, D, !FIT_TOP>(a, stage[wl], lane, tau, true, last,
                                                lane * quarter - (64 * quarter - top_rows),
                                                pid, m, n, rinc, cinc);
     }

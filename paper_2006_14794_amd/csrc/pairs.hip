@@ -205,8 +205,9 @@ __global__ __launch_bounds__(1024) void band_plan_kernel(
 
 // The sentinel into the part of the slot buffers that the bands write: the
 // first n S doubles (n coarse columns of the pair, S fine columns each) of
-// every band task but a pair's last, which hands nothing on.  One workgroup
-// per pair of the band plan; tasks at or past t_max are left alone.
+// every band task but a pair's last, which hands nothing on.  Grid: pairs of the
+// band plan by parts of a pair's tasks (several where the pairs alone are too
+// few workgroups); tasks at or past t_max are left alone.
 __global__ __launch_bounds__(256) void fill_task_slots_kernel(
     uint64_t* __restrict__ tbuf, const int32_t* __restrict__ task_base,
     const int32_t* __restrict__ order, const int32_t* __restrict__ counts,
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256) void fill_task_slots_kernel(
     if (mx <= 0 || my <= 0) continue;  // a single task
     int64_t n = (int64_t)(mx > my ? mx : my) << lam;
     if (n > stride) n = stride;
-    for (int64_t t = t0; t < t1; ++t) {
+    for (int64_t t = t0 + blockIdx.y; t < t1; t += gridDim.y) {
       uint64_t* __restrict__ p = tbuf + t * stride;
       for (int64_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = v;
     }
@@ -245,7 +246,11 @@ hipError_t launch_fill_task_slots(uint64_t* tbuf, const PairPlanArgs& p,
                                   uint64_t v, hipStream_t stream) {
   if (t_max <= 0 || p.npairs <= 0) return hipSuccess;
   const int32_t blocks = p.npairs < 8192 ? p.npairs : 8192;
-  hipLaunchKernelGGL(fill_task_slots_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, tbuf,
+  // at least about 1024 workgroups (five pairs of 62 bands: 19 us, 131 with one
+  // workgroup per pair)
+  const int32_t parts = blocks < 1024 ? 1024 / blocks : 1;
+  hipLaunchKernelGGL(fill_task_slots_kernel, dim3((unsigned)blocks, (unsigned)parts), dim3(256), 0,
+                     stream, tbuf,
                      task_base, p.order, p.counts, p.x_n, p.x_len, p.y_n, p.y_len, p.gram_ny,
                      p.lam, stride, t_max, v);
   return hipGetLastError();
