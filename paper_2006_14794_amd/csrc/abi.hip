@@ -179,20 +179,24 @@ struct SweepShape {
   int64_t run;
 };
 
+// coef: the coefficient sweep, whose steps load a float per coarse row (weighed
+// like two channels) instead of forming inner products.
 SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t n, int lam,
-                              int d, bool implicit, bool sym, bool no_diag, int32_t run) {
+                              int d, bool implicit, bool sym, bool no_diag, int32_t run,
+                              bool coef = false) {
   const int64_t simds = device_simds();
   const int64_t M = fine_rows < 1 ? 1 : fine_rows;
   const int64_t cap = ny < 64 ? (ny < 1 ? 1 : ny) : 64;
   const int64_t tuned = run < ny ? run : (ny > 0 ? ny : 1);
   const int64_t s = sym && no_diag ? 1 : 0;
+  if (coef) d = 2;
   const int dp = sk::padded_dim(d);
   SweepShape best{0, 1, 1};
   double best_cost = 0.0;
   auto consider = [&](int R, int ng, int64_t k) {
     const int gl = 64 / ng, S = 1 << lam, cr = R >= S ? R / S : 1;
     const double step = cr * (0.64 * d + (implicit ? 8.0 : 2.0)) + 2.0 * R * S + 2.0 * S + 16.0;
-    const int regs = 2 * R + cr * d + 3 * dp + 4 * S + 30;
+    const int regs = 2 * R + cr * d + (coef ? 3 * cr : 3 * dp) + 4 * S + 30;
     const int64_t resident = regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
     const int64_t rpr = (ny + k - 1) / k;
     const int64_t runs = sym ? sk::tri_runs(nx - s, rpr, k, s) : nx * rpr;
@@ -207,23 +211,28 @@ SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t
     }
   };
   const int64_t pairs = sym ? nx * (nx + 1) / 2 : nx * ny;
-  for (int ng : {1, 4}) {
-    const int64_t gl = 64 / ng;
-    for (int R : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
-      // more rows than the path's mean less fixed work per row: heights up to
-      // four times the least one
-      if (gl * R < M || gl * R >= 4 * M + 64) continue;
-      if (!sk::forward_fn(implicit, lam, R, ng, d)) continue;
-      // single pairs, and about four waves per SIMD
-      const int64_t k = pairs / (4 * simds * ng);
-      if (run > 0) {
-        consider(R, ng, tuned);
-      } else {
-        consider(R, ng, 1);
-        if (k > 1) consider(R, ng, k < cap ? k : cap);
-        if (k >= 1 && k < cap) consider(R, ng, k + 1);
+  // more rows than the path's mean less fixed work per row: heights up to about
+  // four times the path's, or any where none of these is compiled
+  for (bool any = false; best.R == 0; any = true) {
+    for (int ng : {1, 4}) {
+      const int64_t gl = 64 / ng;
+      for (int R : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
+        if (gl * R < M || (!any && gl * R >= 4 * M + 64)) continue;
+        if (!(coef ? sk::coef_sweep_fn(implicit, lam, R, ng)
+                   : sk::forward_fn(implicit, lam, R, ng, d)))
+          continue;
+        // single pairs, and about four waves per SIMD
+        const int64_t k = pairs / (4 * simds * ng);
+        if (run > 0) {
+          consider(R, ng, tuned);
+        } else {
+          consider(R, ng, 1);
+          if (k > 1) consider(R, ng, k < cap ? k : cap);
+          if (k >= 1 && k < cap) consider(R, ng, k + 1);
+        }
       }
     }
+    if (any) break;
   }
   if (run <= 0 && best.R > 0)
     for (int64_t k = 1; k <= cap; ++k) consider(best.R, best.ng, k);
@@ -388,16 +397,17 @@ constexpr int32_t kMaxFusedDim = 16;
 constexpr size_t kCoefCapBytes = size_t(1) << 30;
 
 struct CoefPlan {
-  int R;
+  int R, ng;
   int32_t lam, rep;
   int32_t run;
-  int64_t runs_per_row, n_waves;
-  int64_t stride;  // floats per wave
+  int64_t runs_per_row, runs;
+  int64_t stride;  // floats per wave (ng runs)
   int64_t chunk;   // waves per producer / sweep launch pair
   size_t coef_off, total;
 };
 
-// mode 0: pairs; 1, 2: Gram (2: upper triangle)
+// mode 0: pairs; 1, 2: Gram (2: upper triangle, with the shape and so the slots
+// of the full Gram, of which it takes fewer)
 CoefPlan coef_plan(const sk_paths* X, const sk_paths* Y, int32_t lam0, int mode) {
   CoefPlan P{};
   const Order o = split_order(lam0);
@@ -405,24 +415,24 @@ CoefPlan coef_plan(const sk_paths* X, const sk_paths* Y, int32_t lam0, int mode)
   P.lam = o.k;
   P.rep = o.rep;
   const int64_t fine_rows = (int64_t)(Xr.len > 1 ? Xr.len - 1 : 1) << o.k;
-  P.R = sk::coef_rows_per_lane(fine_rows, o.k);
   P.coef_off = forward_ws(X, Y);  // unrefined increments and plans
   P.total = P.coef_off;
+  const int64_t ny = mode == 0 ? 1 : Y->n_paths;
+  const SweepShape sh = choose_sweep_shape(
+      X->n_paths, ny, fine_rows, Yr.len > 1 ? Yr.len - 1 : 1, o.k, X->dim, false, false, false,
+      mode == 0 || Y->offsets ? 1 : 0, true);
+  P.R = sh.R;
+  P.ng = sh.ng;
   if (P.R == 0) return P;
-  if (mode == 0) {
-    P.run = 1;
-    P.runs_per_row = 1;
-    P.n_waves = X->n_paths;
-  } else {
-    P.run = Y->offsets ? 1 : (int32_t)choose_run(X->n_paths, Y->n_paths, 0);
-    P.runs_per_row = (Y->n_paths + P.run - 1) / P.run;
-    P.n_waves = X->n_paths * P.runs_per_row;
-  }
+  P.run = (int32_t)sh.run;
+  P.runs_per_row = mode == 0 ? 1 : (ny + P.run - 1) / P.run;
+  P.runs = X->n_paths * P.runs_per_row;
   const int64_t cols = (int64_t)P.run * (Yr.len > 1 ? Yr.len - 1 : 1);
-  P.stride = sk::coef_wave_floats(cols, P.R, o.k);
+  P.stride = sk::coef_wave_floats(cols, P.R, o.k, P.ng);
+  const int64_t waves = (P.runs + P.ng - 1) / P.ng;
   P.chunk = (int64_t)(kCoefCapBytes / ((size_t)P.stride * sizeof(float)));
   if (P.chunk < 1) P.chunk = 1;
-  if (P.chunk > P.n_waves) P.chunk = P.n_waves > 0 ? P.n_waves : 1;
+  if (P.chunk > waves) P.chunk = waves > 0 ? waves : 1;
   P.total = P.coef_off + align256((size_t)P.chunk * (size_t)P.stride * sizeof(float));
   return P;
 }
@@ -695,6 +705,22 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   return e == hipSuccess ? SK_OK : SK_ERR_HIP;
 }
 
+// A symmetric Gram's waves enumerate only the runs of its upper triangle; an
+// unbiased one (diagonal zeroed) leaves the diagonal out of them, and
+// zero_skipped_diagonal writes it.
+void set_triangle(sk::SweepArgs& a, int mode) {
+  if (mode != 2) return;
+  const int64_t s = a.no_diag ? 1 : 0;
+  a.tri = (int32_t)(1 + s);
+  a.n_waves = a.nx > s ? sk::tri_runs(a.nx - s, a.runs_per_row, a.run, s) : 0;
+  a.tri32 = (a.nx + 1) * a.runs_per_row <= INT32_MAX && (a.nx + 1) * a.run <= INT32_MAX ? 1 : 0;
+}
+
+sk_status zero_skipped_diagonal(const sk::SweepArgs& a, hipStream_t stream) {
+  if (a.tri != 2 || !a.out) return SK_OK;
+  return sk::launch_zero_diag(a.out, a.nx, stream) == hipSuccess ? SK_OK : SK_ERR_HIP;
+}
+
 // Any channel count: the increment Gram on the matrix cores, then the
 // coefficient sweep, wave chunk by wave chunk (coef.hip).
 sk_status run_coef(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32_t flags,
@@ -728,34 +754,11 @@ sk_status run_coef(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32_t 
     return SK_ERR_HIP;
   const sk_paths Xr = refined(X, P.rep), Yr = refined(Y, P.rep);
 
-  sk::CoefArgs c{};
-  c.incx = incx;
-  c.incy = incy;
-  c.x_n = X->offsets ? px.n : nullptr;
-  c.x_start = X->offsets ? px.start : nullptr;
-  c.y_n = Y->offsets ? py.n : nullptr;
-  c.y_start = Y->offsets ? py.start : nullptr;
-  c.x_len = Xr.len;
-  c.y_len = Yr.len;
-  c.nx = X->n_paths;
-  c.ny = Y->n_paths;
-  c.mode = mode;
-  c.run = P.run;
-  c.runs_per_row = P.runs_per_row;
-  c.d = d;
-  c.dpad = dp;
-  c.R = P.R;
-  c.lam = P.lam;
-  c.rep = P.rep;
-  c.scale = ldexpf(1.0f, -(2 * P.lam + 1)) / ((float)P.rep * (float)P.rep);
-  c.coef = coef;
-  c.coef_stride = P.stride;
-
   sk::SweepArgs a{};
-  a.x_n = c.x_n;
-  a.x_start = c.x_start;
-  a.y_n = c.y_n;
-  a.y_start = c.y_start;
+  a.x_n = X->offsets ? px.n : nullptr;
+  a.x_start = X->offsets ? px.start : nullptr;
+  a.y_n = Y->offsets ? py.n : nullptr;
+  a.y_start = Y->offsets ? py.start : nullptr;
   a.x_len = Xr.len;
   a.y_len = Yr.len;
   a.nx = X->n_paths;
@@ -769,35 +772,49 @@ sk_status run_coef(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32_t 
   a.out_ld = Y->n_paths;
   a.coef = coef;
   a.coef_stride = P.stride;
-  for (int64_t w0 = 0; w0 < P.n_waves; w0 += P.chunk) {
-    const int64_t nw = (P.n_waves - w0) < P.chunk ? (P.n_waves - w0) : P.chunk;
-    c.wave0 = w0;
-    c.n_waves = nw;
+  a.n_waves = P.runs;
+  set_triangle(a, mode);
+  const int64_t runs = a.n_waves;
+
+  sk::CoefArgs c{};
+  c.incx = incx;
+  c.incy = incy;
+  c.d = d;
+  c.dpad = dp;
+  c.R = P.R;
+  c.lam = P.lam;
+  c.rep = P.rep;
+  c.ng = P.ng;
+  c.scale = ldexpf(1.0f, -(2 * P.lam + 1)) / ((float)P.rep * (float)P.rep);
+  const int64_t step = P.chunk * P.ng;  // runs per chunk
+  for (int64_t r0 = 0; r0 < runs; r0 += step) {
+    a.wave0 = r0;
+    a.n_waves = (runs - r0) < step ? (runs - r0) : step;
+    c.s = a;
+    // workgroups over whole rows where their columns are one stream (and few
+    // enough tiles for a grid's second dimension)
+    c.by_row = mode != 0 && !Y->offsets && P.rep == 1 &&
+               Y->n_paths * (int64_t)(Y->len - 1) <= 128 * (int64_t)65535;
+    if (c.by_row) {
+      auto row_of = [&](int64_t r) -> int64_t {
+        if (!a.tri) return r / a.runs_per_row;
+        int64_t lo = 0, hi = a.nx;  // the last row whose runs start at or before r
+        while (hi - lo > 1) {
+          const int64_t mid = (lo + hi) >> 1;
+          if (sk::tri_runs(mid, a.runs_per_row, a.run, a.tri - 1) <= r) lo = mid; else hi = mid;
+        }
+        return lo;
+      };
+      c.row0 = row_of(r0);
+      c.rows = row_of(r0 + a.n_waves - 1) - c.row0 + 1;
+    }
     if (sk::launch_coef(c, rounding, X->len - 1, Y->len - 1, stream) != hipSuccess)
       return SK_ERR_HIP;
-    a.wave0 = w0;
-    a.n_waves = nw;
-    const hipError_t e = sk::launch_coef_sweep(a, P.lam, P.R, a.implicit != 0, stream);
+    const hipError_t e = sk::launch_coef_sweep(a, P.lam, P.R, P.ng, a.implicit != 0, stream);
     if (e == hipErrorInvalidValue) return SK_ERR_UNSUPPORTED;
     if (e != hipSuccess) return SK_ERR_HIP;
   }
-  return SK_OK;
-}
-
-// A symmetric Gram's waves enumerate only the runs of its upper triangle; an
-// unbiased one (diagonal zeroed) leaves the diagonal out of them, and
-// zero_skipped_diagonal writes it.
-void set_triangle(sk::SweepArgs& a, int mode) {
-  if (mode != 2) return;
-  const int64_t s = a.no_diag ? 1 : 0;
-  a.tri = (int32_t)(1 + s);
-  a.n_waves = a.nx > s ? sk::tri_runs(a.nx - s, a.runs_per_row, a.run, s) : 0;
-  a.tri32 = (a.nx + 1) * a.runs_per_row <= INT32_MAX && (a.nx + 1) * a.run <= INT32_MAX ? 1 : 0;
-}
-
-sk_status zero_skipped_diagonal(const sk::SweepArgs& a, hipStream_t stream) {
-  if (a.tri != 2 || !a.out) return SK_OK;
-  return sk::launch_zero_diag(a.out, a.nx, stream) == hipSuccess ? SK_OK : SK_ERR_HIP;
+  return zero_skipped_diagonal(a, stream);
 }
 
 sk_status run_forward(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32_t flags,

@@ -95,7 +95,7 @@ int choose_rows_for(int kind, int64_t fine_rows, int lam, int dim);
 // own scratch slot.  `fast` runs every task on the reversing kernel with R rows
 // per lane and ng pairs per wave; `redo` then runs the tasks of its list on
 // the recomputing one.  The kGradCounters queue heads at fast.counter (fast's,
-// redo's, the list's length) are zeroed by a kernel first.  ys: form the
+// redo's, the list's length) must be zero.  ys: form the
 // y-side gradients (part_y), else the x side only.
 constexpr int kGradCounters = 3;
 hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng, int lam, int dim,
@@ -201,36 +201,29 @@ hipError_t launch_pairs(const PairArgs& a, int lam, int rows_per_lane, int dim,
                         int64_t max_waves, hipStream_t stream, int blocks_per_cu = 0);
 
 // Coefficient-driven sweep for any number of channels (coef.hip).
-// coef_kernel writes the pre-scaled coarse coefficients of the launched
-// waves in the order coef_sweep_kernel reads them; see coef.hip.
+// coef_kernel writes the pre-scaled coarse coefficients of the launched runs in
+// the order coef_sweep_kernel reads them; see coef.hip.
 struct CoefArgs {
+  SweepArgs s;              // the consuming sweep's work: its runs [wave0, wave0 + n_waves) and
+                            // plans (refined: n rep, start rep), coef, coef_stride
   const float* incx;        // dense unscaled increments (not refined)
   const float* incy;
-  const int32_t* x_n;       // plans of the batch as swept (refined: n rep, start rep)
-  const int64_t* x_start;
-  const int32_t* y_n;
-  const int64_t* y_start;
-  int32_t x_len, y_len;     // points per path as swept (refined)
-  int64_t nx, ny;
-  int32_t mode;             // as SweepArgs
-  int32_t run;
-  int64_t runs_per_row;
-  int64_t wave0, n_waves;   // waves of this launch
   int32_t d, dpad;
-  int32_t R, lam, rep;      // the consuming sweep's rows per lane and order; refinement
+  int32_t R, lam, rep;      // the sweep's rows per lane and order; refinement
+  int32_t ng;               // ... and runs per wave
+  int32_t by_row;           // workgroups over the x paths [row0, row0 + rows) whose runs the
+  int64_t row0, rows;       // launch holds (Grams with a uniform y batch, not refined); else runs
   float scale;              // 2^-(2 lam + 1) / rep^2
-  float* coef;              // per launched wave: coef_stride floats
-  int64_t coef_stride;
 };
-// Rows per lane of the coefficient sweep (R >= 2^lam; 0 if none fits).
-int coef_rows_per_lane(int64_t fine_rows, int lam);
-// Floats of one wave's coefficient slots for a run of total_cols columns.
-int64_t coef_wave_floats(int64_t total_cols, int R, int lam);
+void* coef_sweep_fn(bool implicit, int lam, int R, int ng);
+// Floats of one wave's coefficient slots for runs of total_cols columns.
+int64_t coef_wave_floats(int64_t total_cols, int R, int lam, int ng);
 // max_m, max_n: unrefined increment counts (upper bounds) of the batches.
 hipError_t launch_coef(const CoefArgs& a, int precision, int64_t max_m, int64_t max_n,
                        hipStream_t stream);
-hipError_t launch_coef_sweep(const SweepArgs& a, int lam, int rows_per_lane, bool implicit,
-                             hipStream_t stream, int waves_per_block = 0);
+// a.n_waves counts runs, ng of them per wave.
+hipError_t launch_coef_sweep(const SweepArgs& a, int lam, int rows_per_lane, int ng,
+                             bool implicit, hipStream_t stream, int waves_per_block = 0);
 
 // Reduced measure by proximal gradient (reduce.hip): one workgroup.
 constexpr int kMaxReduceN = 4096;

@@ -36,7 +36,7 @@ struct SweepArgs {
   int64_t wave0;
   // coefficient sweep: per launched wave, coef_stride floats of pre-scaled
   // coarse coefficients in step order ([step][lane][coarse row of the strip])
-  const float* coef;
+  float* coef;
   int64_t coef_stride;
 };
 

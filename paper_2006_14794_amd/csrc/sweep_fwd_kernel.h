@@ -170,17 +170,9 @@ __device__ __forceinline__ I tri_row(const SweepArgs& a, I w, I s) {
   return lo;
 }
 
-// Resolves the run of pairs (x_ia, y_b), b in [b0, b1), of run w, swept by
-// `lanes` lanes of which this is lane `lane`; writes the value of every pair
-// with nothing to sweep (a broken path: NaN; a one-point path: the boundary
-// value 1; 0 on the diagonal of a symmetric Gram without its diagonal, as for
-// swept pairs), and returns false when there are no columns to stream.  m:
-// increments of x_ia; total: columns of the run.  Runs longer than one pair
-// are only formed for uniform y batches, so every pair of a run has the same
-// width.
-__device__ __forceinline__ bool wave_run(const SweepArgs& a, int64_t w, int lane, int rows,
-                                         int lam, int64_t& ia, int64_t& b0, int64_t& b1,
-                                         int32_t& m, int64_t& total, int lanes = 64) {
+// The pairs (x_ia, y_b), b in [b0, b1), of run w (false: none).
+__device__ __forceinline__ bool locate_run(const SweepArgs& a, int64_t w, int64_t& ia,
+                                           int64_t& b0, int64_t& b1) {
   if (a.mode == 0) {
     ia = w;
     b0 = w;
@@ -208,6 +200,21 @@ __device__ __forceinline__ bool wave_run(const SweepArgs& a, int64_t w, int lane
     if (a.mode == 2 && b0 < ia) b0 = ia;
     if (b0 >= b1) return false;
   }
+  return true;
+}
+
+// Resolves the run of pairs (x_ia, y_b), b in [b0, b1), of run w, swept by
+// `lanes` lanes of which this is lane `lane`; writes the value of every pair
+// with nothing to sweep (a broken path: NaN; a one-point path: the boundary
+// value 1; 0 on the diagonal of a symmetric Gram without its diagonal, as for
+// swept pairs), and returns false when there are no columns to stream.  m:
+// increments of x_ia; total: columns of the run.  Runs longer than one pair
+// are only formed for uniform y batches, so every pair of a run has the same
+// width.
+__device__ __forceinline__ bool wave_run(const SweepArgs& a, int64_t w, int lane, int rows,
+                                         int lam, int64_t& ia, int64_t& b0, int64_t& b1,
+                                         int32_t& m, int64_t& total, int lanes = 64) {
+  if (!locate_run(a, w, ia, b0, b1)) return false;
   m = n_inc(a.x_n, a.x_len, ia);
   total = 0;
   for (int64_t b = b0; b < b1; ++b) {
