@@ -1520,19 +1520,19 @@ static sk_status gram_backward(const sk_paths* X, const sk_paths* Y, int32_t dya
   sk::PathPlan py{reinterpret_cast<int32_t*>(base + L.plany_n),
                   reinterpret_cast<int64_t*>(base + L.plany_start)};
   const sk::Batch bx = to_batch(X), by = to_batch(Y);
+  int32_t* counts = reinterpret_cast<int32_t*>(base + P.counts);
   const float scale = ldexpf(1.0f, -(2 * lam + 1));
   if (X->offsets && sk::launch_plan(bx, px, st) != hipSuccess) return SK_ERR_HIP;
   if (Y->offsets && sk::launch_plan(by, py, st) != hipSuccess) return SK_ERR_HIP;
   if (sk::launch_increments_xy(bx, X->offsets ? &px : nullptr, scale, by,
                                Y->offsets ? &py : nullptr, 1.0f, dp, incx, incy, st, sk::kRoundNone,
-                               o.rep) != hipSuccess)
+                               o.rep, counts + 4, sk::kGradCounters) != hipSuccess)
     return SK_ERR_HIP;
   if (X->offsets && sk::launch_scale_plan(px, X->n_paths, o.rep, st) != hipSuccess)
     return SK_ERR_HIP;
   if (Y->offsets && sk::launch_scale_plan(py, Y->n_paths, o.rep, st) != hipSuccess)
     return SK_ERR_HIP;
 
-  int32_t* counts = reinterpret_cast<int32_t*>(base + P.counts);
   int32_t* order = nullptr;
   if (ragged) {
     // one task per pair, costliest first (the ordering only steers scheduling)

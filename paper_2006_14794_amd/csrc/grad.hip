@@ -40,10 +40,6 @@ void* grad_rev_fn(int lam, int R, int ng, int d, bool ys) {
 
 namespace {
 
-__global__ void zero_i32_kernel(int32_t* p, int n) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
-}
-
 // Point gradients of one batch from the increment gradients of a Gram
 // gradient launch, in double, each sum in a fixed order (deterministic):
 //   dinc[k][p] = xscale sum_j part_x[k][j][rows of p]          (x side, j < runs)
@@ -131,9 +127,6 @@ hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng
   auto g = reinterpret_cast<void (*)(const GradArgs)>(grad_fn(lam, d, ys));
   if (!f || !g) return hipErrorInvalidValue;
   if (fast.n_tasks <= 0 || slots <= 0) return hipSuccess;
-  // both queue heads and the redo count
-  hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, stream, fast.counter, kGradCounters);
-  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   // one wave per workgroup: slot = workgroup; every slot's scratch is its own,
   // so any number of them may be resident at once
   hipLaunchKernelGGL(f, dim3((unsigned)slots), dim3(64), 0, stream, fast);

@@ -118,8 +118,15 @@ __device__ __forceinline__ void increments_one(const IncJob& j, int64_t k) {
   }
 }
 
+// Counters that a later kernel of the call needs at zero (a launch saved).
+__device__ __forceinline__ void zero_counters(int32_t* zero, int n) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < n) zero[threadIdx.x] = 0;
+}
+
 // Workgroups [0, jx.n_paths) take the paths of jx, the rest those of jy.
-__global__ __launch_bounds__(256) void increments_kernel(const IncJob jx, const IncJob jy) {
+__global__ __launch_bounds__(256) void increments_kernel(const IncJob jx, const IncJob jy,
+                                                         int32_t* zero, int n_zero) {
+  zero_counters(zero, n_zero);
   const int64_t b = blockIdx.x;
   if (b < jx.n_paths)
     increments_one(jx, b);
@@ -182,7 +189,9 @@ __device__ __forceinline__ void increments4_one(const IncJob& j, int64_t k) {
   }
 }
 
-__global__ __launch_bounds__(256) void increments4_kernel(const IncJob jx, const IncJob jy) {
+__global__ __launch_bounds__(256) void increments4_kernel(const IncJob jx, const IncJob jy,
+                                                          int32_t* zero, int n_zero) {
+  zero_counters(zero, n_zero);
   const int64_t b = blockIdx.x;
   if (b < jx.n_paths)
     increments4_one(jx, b);
@@ -305,16 +314,18 @@ bool four_wide(const IncJob& j) {
 hipError_t launch_increments_xy(const Batch& bx, const PathPlan* planx, float scalex,
                                 const Batch& by, const PathPlan* plany, float scaley, int dpad,
                                 float* incx, float* incy, hipStream_t stream, int rounding,
-                                int rep) {
+                                int rep, int32_t* zero, int n_zero) {
   const IncJob jx = make_job(bx, planx, scalex, dpad, incx, rounding, rep);
   const IncJob jy = make_job(by, plany, scaley, dpad, incy, rounding, rep);
   const int64_t blocks = jx.n_paths + jy.n_paths;
   if (blocks == 0) return hipSuccess;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (four_wide(jx) && four_wide(jy))
-    hipLaunchKernelGGL(increments4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jx, jy);
+    hipLaunchKernelGGL(increments4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jx, jy,
+                       zero, n_zero);
   else
-    hipLaunchKernelGGL(increments_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jx, jy);
+    hipLaunchKernelGGL(increments_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jx, jy,
+                       zero, n_zero);
   return hipGetLastError();
 }
 

@@ -43,12 +43,14 @@ hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
 // that 16-bit format (the inner products then see 16-bit inputs, float32
 // sums).  With rep > 1 (a power of two) every increment fills rep
 // consecutive rows, each scale * (x_{p+1} - x_p) / rep: the batch refined rep
-// times, exactly (rows start[k] rep + p rep + j).
+// times, exactly (rows start[k] rep + p rep + j).  n_zero counters at `zero` are
+// zeroed by the same launch (some batch must have increments).
 enum { kRoundNone = 0, kRoundBf16 = 1, kRoundF16 = 2 };
 hipError_t launch_increments_xy(const Batch& bx, const PathPlan* planx, float scalex,
                                 const Batch& by, const PathPlan* plany, float scaley, int dpad,
                                 float* incx, float* incy, hipStream_t stream,
-                                int rounding = kRoundNone, int rep = 1);
+                                int rounding = kRoundNone, int rep = 1, int32_t* zero = nullptr,
+                                int n_zero = 0);
 // The plan of a batch refined rep times: n[k] -> n[k] rep (for n[k] > 0),
 // start[k] -> start[k] rep.  Run after the increments have read the plan.
 hipError_t launch_scale_plan(PathPlan plan, int64_t n_paths, int rep, hipStream_t stream);
@@ -95,7 +97,7 @@ int choose_rows_for(int kind, int64_t fine_rows, int lam, int dim);
 // own scratch slot.  `fast` runs every task on the reversing kernel with R rows
 // per lane and ng pairs per wave; `redo` then runs the tasks of its list on
 // the recomputing one.  The kGradCounters queue heads at fast.counter (fast's,
-// redo's, the list's length) must be zero.  ys: form the
+// redo's, the list's length) must be zero (launch_increments_xy).  ys: form the
 // y-side gradients (part_y), else the x side only.
 constexpr int kGradCounters = 3;
 hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng, int lam, int dim,
