@@ -1,5 +1,6 @@
 // C ABI of libsigkernel: argument validation, workspace layout, launches.
 // Declarations and contracts: include/sigkernel.h.
+#include <float.h>
 #include <math.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -110,19 +111,6 @@ ForwardLayout forward_layout(const sk_paths* X, const sk_paths* Y) {
 
 size_t forward_ws(const sk_paths* X, const sk_paths* Y) { return forward_layout(X, Y).total; }
 
-// Pairs streamed through one wave for a Gram with a uniform y batch: the
-// tuned value, else enough waves to fill every SIMD about four times, at
-// most 64 pairs per run.
-int64_t choose_run(int64_t nx, int64_t ny, int32_t tuned) {
-  if (tuned > 0) return tuned < ny ? tuned : (ny > 0 ? ny : 1);
-  const int64_t target_waves = 256 * 4 * 4;
-  int64_t run = (nx * ny) / target_waves;
-  if (run < 1) run = 1;
-  if (run > 64) run = 64;
-  if (run > ny) run = ny;
-  return run;
-}
-
 // SIMDs of the current device (four per compute unit); 1024 if unknown.
 int64_t device_simds() {
   int dev = 0, cus = 0;
@@ -131,38 +119,6 @@ int64_t device_simds() {
       cus <= 0)
     return 1024;
   return 4 * (int64_t)cus;
-}
-
-// Pairs streamed through one wave of a one-wave forward Gram sweep: the tuned
-// value, else the run that minimises the busiest SIMD's time.  A run of k
-// pairs over `cols` fine columns each takes about k + 64 / cols pair times
-// (the wavefront fills once per run); the busiest SIMD holds
-// ceil(waves / SIMDs) waves, and a SIMD with one, two or three waves issues
-// at 0.73, 0.93 or 0.97 of its rate with four or more (measured on the
-// sweep).  A symmetric Gram counts only its upper triangle's runs (without
-// the diagonal when that is zeroed).  At most
-// 64 pairs per run; ties go to the shorter run.
-int64_t choose_sweep_run(int64_t nx, int64_t ny, int64_t cols, bool sym, int32_t tuned,
-                         bool no_diag = false) {
-  if (tuned > 0 || ny <= 1 || cols <= 0) return choose_run(nx, ny, tuned);
-  const int64_t simds = device_simds();
-  const double fill = 64.0 / (double)cols;
-  const int64_t cap = ny < 64 ? ny : 64;
-  int64_t best = 1;
-  double best_cost = 0.0;
-  for (int64_t run = 1; run <= cap; ++run) {
-    const int64_t rpr = (ny + run - 1) / run;
-    const int64_t s = sym && no_diag ? 1 : 0;
-    const int64_t waves = sym ? sk::tri_runs(nx - s, rpr, run, s) : nx * rpr;
-    const int64_t per_simd = (waves + simds - 1) / simds;
-    const double rate = per_simd >= 4 ? 1.0 : per_simd == 3 ? 0.97 : per_simd == 2 ? 0.93 : 0.73;
-    const double cost = (double)per_simd * ((double)run + fill) / rate;
-    if (run == 1 || cost < best_cost) {
-      best = run;
-      best_cost = cost;
-    }
-  }
-  return best;
 }
 
 // Rows per lane, runs per wave and pairs per run of a one-wave forward Gram
@@ -179,31 +135,44 @@ struct SweepShape {
   int64_t run;
 };
 
-// coef: the coefficient sweep, whose steps load a float per coarse row (weighed
-// like two channels) instead of forming inner products.
+// kCoef: the coefficient sweep, whose steps load a float per coarse row (weighed
+// like two channels) instead of forming inner products.  kLift: the lifted sweep,
+// d + 25 per node (its distance, exponential and differences) and d + 10 per step.
+// Its wave alone on a SIMD issues at 0.85 of the rate of four (64 x 64 paths of 257
+// points, d = 9, order 1: 652 us, two per SIMD 566) and takes 200 per step however
+// little that holds (60 x 80 paths of 100 points, d = 5, order 1: four rows per
+// lane, one wave per SIMD 201 us, three 183; 16 rows, one wave 159).
+enum SweepKind { kPlain, kCoef, kLift };
 SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t n, int lam,
                               int d, bool implicit, bool sym, bool no_diag, int32_t run,
-                              bool coef = false) {
+                              SweepKind kind = kPlain) {
   const int64_t simds = device_simds();
   const int64_t M = fine_rows < 1 ? 1 : fine_rows;
   const int64_t cap = ny < 64 ? (ny < 1 ? 1 : ny) : 64;
   const int64_t tuned = run < ny ? run : (ny > 0 ? ny : 1);
   const int64_t s = sym && no_diag ? 1 : 0;
-  if (coef) d = 2;
+  const int real_d = d;
+  if (kind == kCoef) d = 2;
   const int dp = sk::padded_dim(d);
   SweepShape best{0, 1, 1};
   double best_cost = 0.0;
   auto consider = [&](int R, int ng, int64_t k) {
     const int gl = 64 / ng, S = 1 << lam, cr = R >= S ? R / S : 1;
-    const double step = cr * (0.64 * d + (implicit ? 8.0 : 2.0)) + 2.0 * R * S + 2.0 * S + 16.0;
-    const int regs = 2 * R + cr * d + (coef ? 3 * cr : 3 * dp) + 4 * S + 30;
-    const int64_t resident = regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
+    const double row = kind == kLift ? d + 25.0 : 0.64 * d;
+    const double issue = cr * (row + (implicit ? 8.0 : 2.0)) + 2.0 * R * S + 2.0 * S + 16.0 +
+                        (kind == kLift ? d + 10 : 0);
+    const int regs = 2 * R + 4 * S + 30 +
+                     (kind == kCoef   ? 5 * cr
+                      : kind == kLift ? (cr * d <= 40 ? 2 : 1) * cr * d + 5 * dp + 4 * cr
+                                      : cr * d + 3 * dp);
+    const int64_t resident = regs <= 128 ? 4 : regs <= 168 ? 3 : regs <= 256 ? 2 : 1;
     const int64_t rpr = (ny + k - 1) / k;
     const int64_t runs = sym ? sk::tri_runs(nx - s, rpr, k, s) : nx * rpr;
     const int64_t waves = (runs + ng - 1) / ng;
     const int64_t per_simd = (waves + simds - 1) / simds;
     const int64_t at_once = per_simd < resident ? per_simd : resident;
-    const double rate = at_once >= 4 ? 1.0 : at_once == 3 ? 0.97 : at_once == 2 ? 0.93 : 0.73;
+    const double step = kind == kLift && at_once == 1 && issue < 200.0 ? 200.0 : issue;
+    const double rate = at_once >= 4 ? 1.0 : at_once == 3 ? 0.97 : at_once == 2 ? 0.93 : kind == kLift ? 0.85 : 0.73;
     const double cost = (double)per_simd * (double)(k * n + gl - 1) * step / rate;
     if (best.R == 0 || cost < best_cost) {
       best = SweepShape{R, ng, k};
@@ -218,8 +187,9 @@ SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t
       const int64_t gl = 64 / ng;
       for (int R : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
         if (gl * R < M || (!any && gl * R >= 4 * M + 64)) continue;
-        if (!(coef ? sk::coef_sweep_fn(implicit, lam, R, ng)
-                   : sk::forward_fn(implicit, lam, R, ng, d)))
+        if (!(kind == kCoef   ? sk::coef_sweep_fn(implicit, lam, R, ng)
+              : kind == kLift ? sk::lifted_fn(lam, R, ng, real_d)
+                              : sk::forward_fn(implicit, lam, R, ng, real_d)))
           continue;
         // single pairs, and about four waves per SIMD
         const int64_t k = pairs / (4 * simds * ng);
@@ -420,7 +390,7 @@ CoefPlan coef_plan(const sk_paths* X, const sk_paths* Y, int32_t lam0, int mode)
   const int64_t ny = mode == 0 ? 1 : Y->n_paths;
   const SweepShape sh = choose_sweep_shape(
       X->n_paths, ny, fine_rows, Yr.len > 1 ? Yr.len - 1 : 1, o.k, X->dim, false, false, false,
-      mode == 0 || Y->offsets ? 1 : 0, true);
+      mode == 0 || Y->offsets ? 1 : 0, kCoef);
   P.R = sh.R;
   P.ng = sh.ng;
   if (P.R == 0) return P;
@@ -1080,8 +1050,7 @@ sk_status run_lifted(const sk_paths* X, const sk_paths* Y, int32_t lam, uint32_t
   const int d = X->dim;
   const int dp = sk::padded_dim(d);
   const int64_t fine_rows = (int64_t)(X->len - 1) << lam;
-  const int R = sk::choose_rows_for(sk::kKernelLifted, fine_rows < 1 ? 1 : fine_rows, lam, d);
-  if (R == 0) return SK_ERR_UNSUPPORTED;
+  if (!sk::lifted_takes(fine_rows, lam, d)) return SK_ERR_UNSUPPORTED;
   const LiftedLayout L = lifted_layout(X, Y);
   if (ws_bytes < L.total) return SK_ERR_WORKSPACE;
   char* base = static_cast<char*>(ws);
@@ -1113,24 +1082,21 @@ sk_status run_lifted(const sk_paths* X, const sk_paths* Y, int32_t lam, uint32_t
   a.mode = mode;
   a.no_diag = (flags & SK_NO_DIAG) ? 1 : 0;
   a.implicit = (flags & SK_IMPLICIT) ? 1 : 0;
-  a.lift_inv = 1.0 / (2.0 * kernel->sigma * kernel->sigma);
-  a.lift_scale = ldexp(1.0, -(2 * lam + 1));
+  // (finite even where 1 / (2 sigma^2) is the largest double: 0 times it is 0)
+  a.lift_log2 = -fmin(1.4426950408889634 / (2.0 * kernel->sigma * kernel->sigma), DBL_MAX);
   a.out = out;
   a.out_ld = Y->n_paths;
-  if (mode == 0) {
-    a.run = 1;
-    a.runs_per_row = 1;
-    a.n_waves = X->n_paths;
-  } else {
-    a.run = Y->offsets ? 1
-                       : (int32_t)choose_sweep_run(X->n_paths, Y->n_paths,
-                                                   (int64_t)(Y->len - 1) << lam, mode == 2, 0,
-                                                   a.no_diag != 0);
-    a.runs_per_row = (Y->n_paths + a.run - 1) / a.run;
-    a.n_waves = X->n_paths * a.runs_per_row;
-    set_triangle(a, mode);
-  }
-  const hipError_t e = sk::launch_lifted(a, lam, R, d, stream, 0);
+  // a pair's stream is one node longer than its columns
+  const int64_t ny_ = mode == 0 ? 1 : Y->n_paths;
+  const SweepShape sh = choose_sweep_shape(X->n_paths, ny_, fine_rows, Y->len, lam, d,
+                                           a.implicit != 0, mode == 2, a.no_diag != 0,
+                                           mode == 0 || Y->offsets ? 1 : 0, kLift);
+  if (sh.R == 0) return SK_ERR_UNSUPPORTED;
+  a.run = (int32_t)sh.run;
+  a.runs_per_row = mode == 0 ? 1 : (Y->n_paths + a.run - 1) / a.run;
+  a.n_waves = X->n_paths * a.runs_per_row;
+  set_triangle(a, mode);
+  const hipError_t e = sk::launch_lifted(a, lam, sh.R, sh.ng, d, stream, 0);
   if (e == hipErrorInvalidValue) return SK_ERR_UNSUPPORTED;
   if (e != hipSuccess) return SK_ERR_HIP;
   return zero_skipped_diagonal(a, stream);

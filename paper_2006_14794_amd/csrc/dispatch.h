@@ -36,6 +36,10 @@ constexpr int max_fitting_rows(int LAM, int D) {
 constexpr bool lifted_fits(int R, int LAM, int D) {
   return (((R >> LAM) > 0 ? (R >> LAM) : 1) + 1) * D <= 96 && R <= 32;
 }
+// ... its heights and runs per wave as the plain sweep's.
+constexpr bool lifted_group_fits(int R, int LAM, int D, int ng) {
+  return lifted_fits(R, LAM, D) && forward_fits(R, LAM, D, ng);
+}
 
 template <class F, int R, int LAM>
 typename F::Fn pick_d(int d) {

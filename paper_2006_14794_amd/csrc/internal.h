@@ -85,12 +85,11 @@ bool forward_takes(int64_t fine_rows, int lam, int dim);
 hipError_t launch_sweep(const SweepArgs& a, int lam, int rows_per_lane, int ng, int dim,
                         hipStream_t stream, int waves_per_block = 0);
 // The sweep of the Gaussian-lifted kernel (lifted_kernel.h): incx / incy hold
-// node rows, lift_inv and lift_scale are set.
-hipError_t launch_lifted(const SweepArgs& a, int lam, int rows_per_lane, int dim,
+// node rows and lift_log2 is set; otherwise as the plain one.
+void* lifted_fn(int lam, int R, int ng, int dim);
+bool lifted_takes(int64_t fine_rows, int lam, int dim);
+hipError_t launch_lifted(const SweepArgs& a, int lam, int rows_per_lane, int ng, int dim,
                          hipStream_t stream, int waves_per_block = 0);
-// Rows per lane of a compiled sweep kernel of the given kind for `fine_rows`
-// rows (0 if none).
-int choose_rows_for(int kind, int64_t fine_rows, int lam, int dim);
 
 // Gradient of weighted Gram entries (grad_rev_kernel.h, grad_kernel.h,
 // grad.hip): persistent waves over the tasks, `slots` of them, each with its
@@ -262,9 +261,9 @@ hipError_t launch_gram_rows(const GramArgs& a, int precision, hipStream_t stream
 constexpr int kGramMfmaMaxDim = 64;
 hipError_t launch_gram_mfma(const GramArgs& a, int precision, hipStream_t stream);
 
-// Compiled sweep kernels (beside forward_fn's) by kind, dyadic order, rows per lane and channels
+// Compiled sweep kernels (beside forward_fn's and lifted_fn's) by kind, dyadic order, rows per lane and channels
 // (nullptr when the configuration is not compiled).
-enum { kKernelPair = 3, kKernelLifted = 4, kKernelPairBand = 6, kKernelPairBandFull = 7 };
+enum { kKernelPair = 3, kKernelPairBand = 6, kKernelPairBandFull = 7 };
 void* sweep_fn(int kind, int lam, int rows_per_lane, int dim);
 
 }  // namespace sk

@@ -22,8 +22,7 @@ struct SweepArgs {
   int32_t mode;             // 0: pairs (x_k, y_k); 1: Gram; 2: Gram upper triangle, mirrored
   int32_t no_diag;          // mode 2: diagonal written as 0
   int32_t implicit;         // 1: the implicit scheme's cell factor (2 + h) / (2 - h)
-  double lift_inv;          // lifted sweep: 1 / (2 sigma^2) of the Gaussian static kernel
-  double lift_scale;        // lifted sweep: 2^-(2 lam + 1), the coefficient's fine-cell factor
+  double lift_log2;         // lifted sweep: -log2(e) / (2 sigma^2) of the Gaussian static kernel
   int32_t run;              // pairs streamed through one wave (Gram with uniform y)
   int64_t runs_per_row;     // ceil(ny / run)
   int32_t tri;       // mode 2: waves enumerate only the runs of the upper triangle

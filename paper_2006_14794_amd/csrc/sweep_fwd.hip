@@ -7,16 +7,16 @@ namespace sk {
 
 #define SK_DECL(k, l) void* sweep_fn_k##k##_l##l##_(int R, int d);
 SK_DECL(3, 0) SK_DECL(3, 1) SK_DECL(3, 2) SK_DECL(3, 3)
-SK_DECL(4, 0) SK_DECL(4, 1) SK_DECL(4, 2) SK_DECL(4, 3)
 SK_DECL(6, 0) SK_DECL(6, 1) SK_DECL(6, 2) SK_DECL(6, 3)
 SK_DECL(7, 0) SK_DECL(7, 1) SK_DECL(7, 2) SK_DECL(7, 3)
 #undef SK_DECL
 #define SK_DECL(k, l) void* sweep_fn_k##k##_l##l##_g1(int R, int d); void* sweep_fn_k##k##_l##l##_g4(int R, int d);
 SK_DECL(0, 0) SK_DECL(0, 1) SK_DECL(0, 2) SK_DECL(0, 3)
+SK_DECL(4, 0) SK_DECL(4, 1) SK_DECL(4, 2) SK_DECL(4, 3)
 SK_DECL(5, 0) SK_DECL(5, 1) SK_DECL(5, 2) SK_DECL(5, 3)
 #undef SK_DECL
 
-void* none_(int, int) { return nullptr; }  // kinds 1 and 2 are not compiled, 0 and 5 by forward_fn
+void* none_(int, int) { return nullptr; }  // kinds 1 and 2 are not compiled, 0, 4 and 5 by forward_fn and lifted_fn
 
 void* sweep_fn(int kind, int lam, int R, int d) {
   using Pick = void* (*)(int, int);
@@ -25,7 +25,7 @@ void* sweep_fn(int kind, int lam, int R, int d) {
       {none_, none_, none_, none_},
       {none_, none_, none_, none_},
       {sweep_fn_k3_l0_, sweep_fn_k3_l1_, sweep_fn_k3_l2_, sweep_fn_k3_l3_},
-      {sweep_fn_k4_l0_, sweep_fn_k4_l1_, sweep_fn_k4_l2_, sweep_fn_k4_l3_},
+      {none_, none_, none_, none_},
       {none_, none_, none_, none_},
       {sweep_fn_k6_l0_, sweep_fn_k6_l1_, sweep_fn_k6_l2_, sweep_fn_k6_l3_},
       {sweep_fn_k7_l0_, sweep_fn_k7_l1_, sweep_fn_k7_l2_, sweep_fn_k7_l3_}};
@@ -33,27 +33,35 @@ void* sweep_fn(int kind, int lam, int R, int d) {
   return table[kind][lam](R, d);
 }
 
-void* forward_fn(bool implicit, int lam, int R, int ng, int d) {
+namespace {
+void* grouped_fn(int kind, int lam, int R, int ng, int d) {
   using Pick = void* (*)(int, int);
 #define SK_ROW(k, l) {sweep_fn_k##k##_l##l##_g1, sweep_fn_k##k##_l##l##_g4}
-  static const Pick table[2][4][2] = {{SK_ROW(0, 0), SK_ROW(0, 1), SK_ROW(0, 2), SK_ROW(0, 3)},
-                                      {SK_ROW(5, 0), SK_ROW(5, 1), SK_ROW(5, 2), SK_ROW(5, 3)}};
+#define SK_KIND_ROWS(k) {SK_ROW(k, 0), SK_ROW(k, 1), SK_ROW(k, 2), SK_ROW(k, 3)}
+  static const Pick table[3][4][2] = {SK_KIND_ROWS(0), SK_KIND_ROWS(5), SK_KIND_ROWS(4)};
+#undef SK_KIND_ROWS
 #undef SK_ROW
   if (lam < 0 || lam > 3 || (ng != 1 && ng != 4)) return nullptr;
-  return table[implicit ? 1 : 0][lam][ng == 1 ? 0 : 1](R, d);
+  return table[kind][lam][ng == 1 ? 0 : 1](R, d);
 }
+}  // namespace
+
+void* forward_fn(bool implicit, int lam, int R, int ng, int d) {
+  return grouped_fn(implicit ? 1 : 0, lam, R, ng, d);
+}
+void* lifted_fn(int lam, int R, int ng, int d) { return grouped_fn(2, lam, R, ng, d); }
 
 bool forward_takes(int64_t fine_rows, int lam, int d) {
   return lam >= 0 && lam <= 3 && d >= 1 && d <= 16 &&
          fine_rows <= 64 * (int64_t)max_fitting_rows(lam, d);
 }
 
-int choose_rows_for(int kind, int64_t fine_rows, int lam, int d) {
-  for (int R = 1; R <= kMaxRowsPerLane; R *= 2) {
-    if (64 * (int64_t)R < fine_rows) continue;
-    return sweep_fn(kind, lam, R, d) ? R : 0;
-  }
-  return 0;
+bool lifted_takes(int64_t fine_rows, int lam, int d) {
+  if (lam < 0 || lam > 3 || d < 1 || d > 16) return false;
+  int r = 0;
+  for (int R = 1; R <= kMaxRowsPerLane; R *= 2)
+    if (lifted_fits(R, lam, d)) r = R;
+  return fine_rows <= 64 * (int64_t)r;
 }
 
 namespace {
@@ -74,9 +82,9 @@ hipError_t launch_sweep(const SweepArgs& a, int lam, int R, int ng, int d, hipSt
                         waves_per_block);
 }
 
-hipError_t launch_lifted(const SweepArgs& a, int lam, int R, int d, hipStream_t stream,
+hipError_t launch_lifted(const SweepArgs& a, int lam, int R, int ng, int d, hipStream_t stream,
                          int waves_per_block) {
-  return launch_forward(sweep_fn(kKernelLifted, lam, R, d), a, 1, stream, waves_per_block);
+  return launch_forward(lifted_fn(lam, R, ng, d), a, ng, stream, waves_per_block);
 }
 
 }  // namespace sk

@@ -1,7 +1,7 @@
 // Instantiations of one sweep kernel (SK_KIND: 0 forward, 3 persistent pairs,
 // 4 lifted forward, 5 implicit forward, 6 pipelined bands with a fitted top
 // band, 7 pipelined bands of one height) at one dyadic order SK_LAM and, for
-// kinds 0 and 5, SK_NG runs per wave.  Included by sweep_k{kind}_l{lam}.hip (one
+// kinds 0, 4 and 5, SK_NG runs per wave.  Included by sweep_k{kind}_l{lam}.hip (one
 // run per wave) and sweep_k{kind}_l{lam}_g4.hip so that the configurations
 // compile in parallel translation units.
 #include "dispatch.h"
@@ -71,8 +71,8 @@ struct Lifted {
   using Fn = void*;
   template <int R, int LAM, int D>
   static Fn get() {
-    if constexpr (lifted_fits(R, LAM, D))
-      return reinterpret_cast<void*>(&lift::lifted_sweep_kernel<R, LAM, D>);
+    if constexpr (lifted_group_fits(R, LAM, D, SK_NG))
+      return reinterpret_cast<void*>(&lift::lifted_sweep_kernel<R, LAM, D, SK_NG>);
     else
       return nullptr;
   }
@@ -88,7 +88,7 @@ void* pick_fixed_lam(int R, int d) {
     case 8: return pick_d<F, 8, SK_LAM>(d);
     case 16: return pick_d<F, 16, SK_LAM>(d);
     case 32: return pick_d<F, 32, SK_LAM>(d);
-#if SK_KIND == 0 || SK_KIND == 5
+#if SK_KIND == 0 || SK_KIND == 4 || SK_KIND == 5
     case 3: return pick_d<F, 3, SK_LAM>(d);
     case 5: return pick_d<F, 5, SK_LAM>(d);
     case 6: return pick_d<F, 6, SK_LAM>(d);
@@ -110,7 +110,9 @@ void* SK_CAT(SK_CAT(SK_CAT(sweep_fn_k0_l, SK_LAM), _g), SK_NG)(int R, int d) {
 #elif SK_KIND == 3
 void* SK_CAT(SK_CAT(sweep_fn_k3_l, SK_LAM), _)(int R, int d) { return pick_fixed_lam<Pair>(R, d); }
 #elif SK_KIND == 4
-void* SK_CAT(SK_CAT(sweep_fn_k4_l, SK_LAM), _)(int R, int d) { return pick_fixed_lam<Lifted>(R, d); }
+void* SK_CAT(SK_CAT(SK_CAT(sweep_fn_k4_l, SK_LAM), _g), SK_NG)(int R, int d) {
+  return pick_fixed_lam<Lifted>(R, d);
+}
 #elif SK_KIND == 5
 void* SK_CAT(SK_CAT(SK_CAT(sweep_fn_k5_l, SK_LAM), _g), SK_NG)(int R, int d) {
   return pick_fixed_lam<FwdImplicit>(R, d);
