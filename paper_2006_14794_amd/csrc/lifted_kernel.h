@@ -220,7 +220,8 @@ __global__ __launch_bounds__(256) void lifted_sweep_kernel(const SweepArgs a) {
 
   // kernel values carry the coefficient's fine-cell factor 2^-(2 lambda + 1)
   constexpr int kShift = 2 * LAM + 1;
-  auto step = [&](auto nearby, float (&yn)[DP], float (&refill)[DP]) {
+  auto step = [&](auto nearby, float (&yn)[DP], float (&refill)[DP])
+                  __attribute__((always_inline)) {
     load_row<DP>(yp + 2 * DP, refill);
     double yd[D];
 #pragma unroll
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(256) void lifted_sweep_kernel(const SweepArgs a) {
     // after another)
 #pragma unroll
     for (int c = 0; c < CR; ++c) asm volatile("" : "+v"(kv[c]));
-    auto own_node = [&]() {
+    auto own_node = [&]() __attribute__((always_inline)) {
       double z[1] = {0.0};
 #pragma unroll
       for (int k = 0; k < D; ++k) {
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(256) void lifted_sweep_kernel(const SweepArgs a) {
     yp += DP;
   };
 
-  auto steps = [&](auto nearby) {
+  auto steps = [&](auto nearby) __attribute__((always_inline)) {
     for (int32_t t = 0; t < nsteps; t += 3) {
       step(nearby, yA, yC);
       step(nearby, yB, yA);
