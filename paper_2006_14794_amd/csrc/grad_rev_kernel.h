@@ -96,6 +96,8 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
   constexpr int YR = C + GL - 1;          // y rows of a segment, per group
   constexpr int Y4 = NG * YR * DP / 4;    // float4s of a segment's y rows
   constexpr int PY = (Y4 + 63) / 64;      // ... per lane
+  constexpr int YQ = DP / 4 | 1;          // float4s from one y row in LDS to the next: odd, since
+                                          // neighbouring lanes read neighbouring rows
   constexpr int NB = C * S;               // lane 0's upper neighbours per segment (NG == 1)
   constexpr int PB = (NB + 63) / 64;
   constexpr int NK = NG * C * S;          // the last lanes' bottom nodes per segment
@@ -106,17 +108,18 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
   constexpr int PL = (NL + 63) / 64;
   constexpr int NW = NG == 1 && NL > NK ? NL : NK;
   constexpr int YW = NG == 1 ? 128 : 64;  // columns of the y-side ring: at least C + GL - 1
+  constexpr int YL = YW + 1;              // ... and doubles from one channel to the next
   constexpr int NY = NG * C * D;          // y-side sums completed by a segment
   constexpr int PO = (NY + 63) / 64;
   static_assert(YW >= C + GL - 1, "y-side ring");
   static_assert(C % 2 == 0 && C <= 32 && KS == grad_rev_state_doubles(R, LAM), "scratch geometry");
-  __shared__ float4 sy[Y4];    // the segment's y rows, zero outside the task
+  __shared__ float4 sy[NG * YR * YQ];  // the segment's y rows, zero outside the task
   __shared__ double sb[NG == 1 ? NB : 1];  // [step][fine column]: lane 0's upper neighbours
   __shared__ double skn[NK];   // [group][step][fine column]: bottom nodes of the last lane's strip
   __shared__ double sl[NG == 1 ? NL : 1];  // [step][LW]: lane 63's lower neighbours
   __shared__ double sw[NW];    // outputs of the segment
   __shared__ double spe[(R + 1) * 64];  // [node][lane]: the strips' nodes at a pair's last column
-  __shared__ double ring[YS ? NG * YW * D : 1];  // [group][column mod YW][channel]: y-side sums
+  __shared__ double ring[YS ? NG * D * YL : 1];  // [group][channel][column mod YW]: y-side sums
 
   const int lane = threadIdx.x;
   const int lg = lane & (GL - 1), grp = lane / GL;
@@ -224,7 +227,7 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
 #pragma unroll
       for (int i = 0; i < PY; ++i) {
         const int e = lane + 64 * i;
-        if (e < Y4) sy[e] = py[i];
+        if (e < Y4) sy[e / (DP / 4) * YQ + e % (DP / 4)] = py[i];
       }
     };
     // lane 0's upper neighbours at steps t0 .. t0 + C - 1 (columns t0 + j; 1
@@ -249,7 +252,7 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
     };
     // the y row of a lane at step t0 + j
     auto get_dy = [&](int j, float (&dy)[DP]) {
-      const float4* r = &sy[(grp * YR + j - lg + GL - 1) * (DP / 4)];
+      const float4* r = &sy[(grp * YR + j - lg + GL - 1) * YQ];
 #pragma unroll
       for (int c = 0; c < DP / 4; ++c) {
         const float4 f = r[c];
@@ -518,10 +521,13 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
       // The y-side sums of a column, sum_p dG[p][q] dx_p, collect in an LDS
       // ring: each lane adds its strip's part at the step it meets the column
       // (the last lane first, so in a fixed order), and a column is complete
-      // when the first lane has passed it.  Passing partial sums from lane to
+      // when the first lane has passed it.  Neighbouring lanes add to neighbouring
+      // columns of a channel, that is to neighbouring banks (a column's channels
+      // side by side put lanes on the same banks: 48 x 40 paths of 120 points, 16
+      // channels, order 1 1657 us for the whole call against 524).  Passing partial sums from lane to
       // lane by DPP cost three instructions per channel and step.
       if constexpr (YS) {
-        for (int e = lane; e < NG * YW * D; e += 64) ring[e] = 0.0;
+        for (int e = lane; e < NG * D * YL; e += 64) ring[e] = 0.0;
       }
 
       float4 py[PY];
@@ -670,13 +676,13 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
             for (int k = 0; k < D; ++k)
               dxacc[c][k] = __builtin_fma(dg[c], (double)dy[k], dxacc[c][k]);
           if constexpr (YS) {
-            double* yr = &ring[(grp * YW + ((t0 + j - lg) & (YW - 1))) * D];
+            double* yr = &ring[grp * D * YL + ((t0 + j - lg) & (YW - 1))];
 #pragma unroll
             for (int k = 0; k < D; ++k) {
               double t = dg[0] * dxd[0][k];
 #pragma unroll
               for (int c = 1; c < CR; ++c) t = __builtin_fma(dg[c], dxd[c][k], t);
-              __hip_atomic_fetch_add(&yr[k], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              __hip_atomic_fetch_add(&yr[k * YL], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
           }
           // the first lane's outputs for the band above
@@ -730,7 +736,7 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
               const uint32_t o = y_slot(e, col);
               const int q = NG == 1 ? 0 : e / (C * D);
               const int e1 = e - q * (C * D);
-              double& r = ring[(q * YW + ((t0 + e1 / D) & (YW - 1))) * D + e1 % D];
+              double& r = ring[(q * D + e1 % D) * YL + ((t0 + e1 / D) & (YW - 1))];
               if (col >= 0) at(pyt, o) = NG == 1 ? po[NG == 1 ? i : 0] + r : r;
               r = 0.0;
             }
