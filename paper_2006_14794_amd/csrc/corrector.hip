@@ -9,9 +9,9 @@
 //              (v_mfma_f32_32x32x16_bf16: bf16 weights and activations,
 //              float32 accumulation), bias and ReLU fused; NHWC bf16
 //              activations (every consumer reads them as bf16).
-//   fused      inference: one workgroup per pair runs all four layers and
-//              the head with the feature map, layer 1's output and each
-//              layer's weights in LDS.
+//   fused      inference: a workgroup per compute unit runs all four layers and
+//              the head of a stream of pairs, the maps in LDS and the weights in
+//              registers.
 //   backward   float32 VALU: input gradients by gathering the (at most four)
 //              taps that reach an input pixel, weight gradients as
 //              per-workgroup partial sums over LDS-staged positions reduced
@@ -242,10 +242,9 @@ __device__ __forceinline__ float bf16r(float v) { return (float)(bf16)v; }
 // selects 8 of the 16 reduction indices of an instruction: for Cin = 32 one
 // tap's channels c0 + 8 half .. + 8, for Cin = 8 tap 2 s + half of
 // instruction s (a tenth tap is zero).  `in` is the pair's [HI][HI][Cin]
-// bf16 map and `w` the layer's [32][9][Cin] weights (bf16, or float32
-// rounded on load), either in global memory or in LDS.
-template <int CIN, int HI, class TW>
-__device__ __forceinline__ void conv_tile(const bf16* in, const TW* w, int t, int lane,
+// bf16 map and `w` the layer's [32][9][Cin] float32 weights, rounded on load.
+template <int CIN, int HI>
+__device__ __forceinline__ void conv_tile(const bf16* in, const float* w, int t, int lane,
                                           f32x16& acc) {
   constexpr int HO = HI / 2, PPP = HO * HO;
   const int row = lane & 31, half = lane >> 5;
@@ -313,106 +312,207 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(const ConvArgs a) {
 }
 
 // ------------------------------------------------------ fused inference --
-// Persistent workgroups of 8 waves, one pair at a time: the feature map,
-// layer 1's output and the current layer's weights stay in LDS; layer 2's
-// output reuses the feature map's space and layers 3-4 that of layer 1; only
-// the two outputs leave the chip.  While a pair is evaluated, waves 4-7 hold
-// the next pair's feature map in registers (loaded at the start, written to
-// LDS once layer 3 has read the feature map's space), and waves 0-3 stage the
-// weights: a wave's global loads complete in order, so the waves that wait on
-// weight loads must not be the ones with the feature loads in flight.
+// Persistent workgroups of 8 waves, one per compute unit, each with a stream of
+// pairs; only the two outputs of a pair leave the chip.  All weights stay in
+// registers for the whole kernel: every wave holds layer 1's and layer 2's
+// operands, waves 1 and 2 layer 3's and wave 0 layer 4's.  The layers of
+// successive pairs overlap, so that a pair takes two barriers:
+//   A: layer 1 of pair i (its 32 tiles split so that the four SIMDs issue about
+//      the same); waves 1, 2: layer 3 of pair i - 1; wave 0: layer 4 of pair
+//      i - 2; wave 3: the head of pair i - 3
+//   B: pair i + 1's feature map from registers to LDS, the loads of pair i + 2's;
+//      layer 2 of pair i, one tile per wave
+// The weights are the matrix operand A and the positions B: a lane's results are
+// then 16 channels of one position, stored as four 8-byte words instead of 16
+// halves.  A map's even columns come before its odd ones (a stride-2 tap reads
+// every other column) and the four 16-byte chunks of a 32-channel pixel are
+// rotated with the pixel's index, so that 16 lanes read 16 different chunks of
+// a 256-byte line of banks.
+//
+// Bound: LDS traffic and the latency of the two phases (reading the feature
+// maps, 512 MB, takes 112 us).  8192 pairs: 220 us; 490 with the weights of each
+// layer staged in LDS for every pair and nine barriers.
 constexpr int kNetThreads = 512;
-constexpr int kLdsF = kFeatFloats;              // feature map, later layer 2
-constexpr int kLdsA1 = 32 * 32 * kCout;         // layer 1 output, later layers 3-4
-constexpr int kLdsW = kCout * 9 * 32;           // one layer's weights
-constexpr int kStageThreads = 256;              // waves 0-3
-constexpr int kFeat16 = kFeatFloats / 8;        // 16-byte chunks of a feature map
-constexpr int kPre = kFeat16 / (kNetThreads - kStageThreads);  // per thread of waves 4-7
-static_assert(kPre * (kNetThreads - kStageThreads) == kFeat16, "feature map split");
+constexpr int kFeat16 = kFeatFloats / 8;  // 16-byte chunks of a feature map
+constexpr int kPre = kFeat16 / kNetThreads;
+static_assert(kPre * kNetThreads == kFeat16, "feature map split");
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // stays in registers
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-template <int CIN>
-__device__ __forceinline__ void stage_weights(bf16* W, const bf16* src, int tid) {
-  constexpr int N16 = kCout * 9 * CIN / 8;  // 16-byte chunks
-  if (tid >= kStageThreads) return;
-  for (int i = tid; i < N16; i += kStageThreads)
-    reinterpret_cast<uint4*>(W)[i] = reinterpret_cast<const uint4*>(src)[i];
+// LDS in 16-byte chunks: feature map, outputs of layers 1, 2, 3 (two pairs),
+// 4 (two pairs), a chunk of zeros; then the biases and the head in float32.
+constexpr int kNetA1 = kFeat16;
+constexpr int kNetA2 = kNetA1 + 32 * 32 * kCout / 8;
+constexpr int kNetA3 = kNetA2 + 16 * 16 * kCout / 8;
+constexpr int kNetA4 = kNetA3 + 2 * 8 * 8 * kCout / 8;
+constexpr int kNetZero = kNetA4 + 2 * 4 * 4 * kCout / 8;
+constexpr int kNetF32 = (kNetZero + 1) * 4;                      // in floats
+constexpr int kNetHead = kNetF32 + kLayers * kCout;
+constexpr int kNetFloats = kNetHead + 2 * kHeadIn + 2;
+
+// the pixel at column wi of row hi of a map W columns wide, and its chunk q
+template <int W>
+__device__ __forceinline__ int map_pixel(int hi, int wi) {
+  return hi * W + (wi & 1) * (W / 2) + (wi >> 1);
+}
+__device__ __forceinline__ int map_chunk(int p, int q) { return 4 * p + (q ^ ((p >> 2) & 3)); }
+
+// A 32-channel layer's tile t: weights w (the lane's 18 operands), input map of
+// side HI at chunk `in`.
+template <int HI>
+__device__ __forceinline__ void net_tile(const bf16x8* lds, int in, const bf16x8 (&w)[18], int t,
+                                         int lane, f32x16& acc) {
+  constexpr int HO = HI / 2, PPP = HO * HO;
+  const int half = lane >> 5;
+  const int pos = t * 32 + (lane & 31);
+  const int ho = pos / HO, wo = pos % HO;
+  const int p0 = (2 * ho - 1) * HI + wo;
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) {
+    const int kh = tap / 3, kw = tap % 3;
+    // column 2 wo - 1 + kw
+    const int p = p0 + kh * HI + (kw == 1 ? 0 : HI / 2) - (kw == 0 ? 1 : 0);
+    const bool out = (PPP < 32 && pos >= PPP) || (kh == 0 && ho == 0) || (kw == 0 && wo == 0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int e = out ? kNetZero : in + map_chunk(p, 2 * c + half);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[2 * tap + c], lds[e], acc, 0, 0, 0);
+    }
+  }
+}
+
+// bias + ReLU, rounded to bf16: channels 8 q + 4 half .. + 4 of a lane's position
+// to chunk `chunk(q)`
+template <class Chunk>
+__device__ __forceinline__ void net_store(const f32x16& acc, const float* bias, bf16x8* lds,
+                                          int half, Chunk chunk) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 b = *reinterpret_cast<const float4*>(bias + 8 * q + 4 * half);
+    bf16x4 v;
+    v[0] = (bf16)fmaxf(acc[4 * q + 0] + b.x, 0.0f);
+    v[1] = (bf16)fmaxf(acc[4 * q + 1] + b.y, 0.0f);
+    v[2] = (bf16)fmaxf(acc[4 * q + 2] + b.z, 0.0f);
+    v[3] = (bf16)fmaxf(acc[4 * q + 3] + b.w, 0.0f);
+    reinterpret_cast<bf16x4*>(lds)[2 * chunk(q) + half] = v;
+  }
 }
 
 __global__ __launch_bounds__(kNetThreads) void net_fused_kernel(const NetArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 lds[kLdsF + kLdsA1 + kLdsW];
-  bf16* F = lds;
-  bf16* A1 = lds + kLdsF;
-  bf16* W = lds + kLdsF + kLdsA1;
-  bf16* A2 = F;                 // 16 x 16 x 32
-  bf16* A3 = A1;                // 8 x 8 x 32
-  bf16* A4 = A1 + 8 * 8 * 32;   // 4 x 4 x 32
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  // the biases of the four layers (the same for every pair)
-  float bias[4];
-  bias[0] = a.params[param_offset(0) + kCout * 9 * 8 + (lane & 31)];
+  __shared__ __attribute__((aligned(16))) float smem[kNetFloats];
+  bf16x8* lds = reinterpret_cast<bf16x8*>(smem);
+  const float* bias = smem + kNetF32;
+  const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t count = ((int64_t)a.n - blockIdx.x + gridDim.x - 1) / gridDim.x;  // pairs
+  auto map_of = [&](int64_t i) {
+    return reinterpret_cast<const u32x4*>(
+        a.feats + ((int64_t)blockIdx.x + i * gridDim.x) * (int64_t)kFeatFloats);
+  };
+  auto feat_chunk = [&](int j) {  // where this thread's j-th chunk of a map goes
+    const int e = tid + j * kNetThreads;
+    return map_pixel<64>(e >> 6, e & 63);
+  };
+
+  bf16x8 w1[5], w2[18], w34[18];
+  {
+    const int row = tid & 31, half = (tid >> 5) & 1;
+    const bf16x8* src = reinterpret_cast<const bf16x8*>(a.wb + param_offset(0)) + row * 9;
 #pragma unroll
-  for (int l = 1; l < 4; ++l) bias[l] = a.params[param_offset(l) + kCout * 9 * 32 + (lane & 31)];
-  if ((int64_t)blockIdx.x < a.n) {
-    const uint4* src = reinterpret_cast<const uint4*>(a.feats + blockIdx.x * (int64_t)kFeatFloats);
-    for (int i = tid; i < kFeat16; i += kNetThreads) reinterpret_cast<uint4*>(F)[i] = src[i];
+    for (int s = 0; s < 5; ++s) {
+      const int tap = 2 * s + half;
+      const bf16x8 v = src[tap < 9 ? tap : 0];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) w1[s][k] = tap < 9 ? v[k] : (bf16)0.0f;
+    }
+    src = reinterpret_cast<const bf16x8*>(a.wb + param_offset(1)) + row * 36 + half;
+#pragma unroll
+    for (int i = 0; i < 18; ++i) w2[i] = src[2 * i];
+    src = reinterpret_cast<const bf16x8*>(a.wb + param_offset(wid == 0 ? 3 : 2)) + row * 36 + half;
+#pragma unroll
+    for (int i = 0; i < 18; ++i) w34[i] = src[2 * i];
   }
-  for (int64_t pn = blockIdx.x; pn < a.n; pn += gridDim.x) {
-    const int64_t nx = pn + gridDim.x;
-    const bool pre = wid >= 4 && nx < a.n;
-    u32x4 next[kPre];
-    if (pre) {
-      const u32x4* src = reinterpret_cast<const u32x4*>(a.feats + nx * (int64_t)kFeatFloats);
+  for (int i = tid; i < kLayers * kCout; i += kNetThreads)
+    smem[kNetF32 + i] =
+        a.params[param_offset(i / kCout) + kCout * 9 * kLayerCin[i / kCout] + i % kCout];
+  for (int i = tid; i < 2 * kHeadIn + 2; i += kNetThreads)
+    smem[kNetHead + i] = a.params[kHeadOffset + i];
+  if (tid < 4) smem[4 * kNetZero + tid] = 0.0f;
+  u32x4 next[kPre];
+  if (count > 0) {
+    const u32x4* src = map_of(0);
 #pragma unroll
-      for (int j = 0; j < kPre; ++j)
-        next[j] = src[(tid - kStageThreads) + j * (kNetThreads - kStageThreads)];
-    }
-    stage_weights<8>(W, a.wb + param_offset(0), tid);
-    __syncthreads();
-    for (int t = wid; t < 32; t += 8) {  // layer 1: 64 x 64 x 8 -> 32 x 32 x 32
-      f32x16 acc = {};
-      conv_tile<8, 64>(F, W, t, lane, acc);
-      store_tile<32 * 32>(acc, bias[0], A1, t, lane);
-    }
-    __syncthreads();
-    stage_weights<32>(W, a.wb + param_offset(1), tid);
-    __syncthreads();
-    {
-      f32x16 acc = {};
-      conv_tile<32, 32>(A1, W, wid, lane, acc);
-      store_tile<16 * 16>(acc, bias[1], A2, wid, lane);
-    }
-    __syncthreads();
-    stage_weights<32>(W, a.wb + param_offset(2), tid);
-    __syncthreads();
-    if (wid < 2) {
-      f32x16 acc = {};
-      conv_tile<32, 16>(A2, W, wid, lane, acc);
-      store_tile<8 * 8>(acc, bias[2], A3, wid, lane);
-    }
-    __syncthreads();
-    // the feature map's space is free: the next pair's map goes in
-    if (pre) {
+    for (int j = 0; j < kPre; ++j) next[j] = src[tid + j * kNetThreads];
 #pragma unroll
-      for (int j = 0; j < kPre; ++j)
-        reinterpret_cast<u32x4*>(F)[(tid - kStageThreads) + j * (kNetThreads - kStageThreads)] =
-            next[j];
+    for (int j = 0; j < kPre; ++j) reinterpret_cast<u32x4*>(lds)[feat_chunk(j)] = next[j];
+  }
+  if (count > 1) {
+    const u32x4* src = map_of(1);
+#pragma unroll
+    for (int j = 0; j < kPre; ++j) next[j] = src[tid + j * kNetThreads];
+  }
+  // layer 1's tiles of this wave
+  const int first = wid < 3 ? 2 * wid : 5 * wid - 9;
+  const int past = wid < 3 ? first + 2 : wid == 7 ? 32 : first + 5;
+  __syncthreads();
+
+  for (int64_t i = 0; i < count + 3; ++i) {
+    // (opaque: operand addresses are formed where they are used, not held in
+    // registers over the loop)
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const int half = lane >> 5;
+    // ---- A
+    if (i < count) {  // layer 1: 64 x 64 x 8 -> 32 x 32 x 32, a tile is one output row
+      const int wo = lane & 31;
+      int base[5];
+      bool out[5];
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {  // tap 2 s + half of output row 0
+        const int tap = 2 * s + half, kh = tap / 3, kw = tap % 3;
+        base[s] = (kh - 1) * 64 + (kw == 1 ? 0 : 32) - (kw == 0 ? 1 : 0) + wo;
+        out[s] = tap == 9 || (kw == 0 && wo == 0);
+      }
+      for (int t = first; t < past; ++t) {
+        f32x16 acc = {};
+#pragma unroll
+        for (int s = 0; s < 5; ++s) {
+          // above row 0: taps 0 .. 2 of the first output row
+          const bool above = t == 0 && (s == 0 || (s == 1 && half == 0));
+          const int e = out[s] || above ? kNetZero : t * 128 + base[s];
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[s], lds[e], acc, 0, 0, 0);
+        }
+        const int p = map_pixel<32>(t, wo);
+        net_store(acc, bias, lds, half, [&](int q) { return kNetA1 + map_chunk(p, q); });
+      }
     }
-    stage_weights<32>(W, a.wb + param_offset(3), tid);
-    __syncthreads();
-    if (wid == 0) {
+    if ((wid == 1 || wid == 2) && i >= 1 && i <= count) {  // layer 3: 8 x 8 x 32
       f32x16 acc = {};
-      conv_tile<32, 8>(A3, W, 0, lane, acc);
-      store_tile<4 * 4>(acc, bias[3], A4, 0, lane);
+      const int t = wid - 1, pos = 32 * t + (lane & 31);
+      net_tile<16>(lds, kNetA2, w34, t, lane, acc);
+      const int p = map_pixel<8>(pos >> 3, pos & 7);
+      const int to = kNetA3 + (int)((i - 1) & 1) * (8 * 8 * kCout / 8);
+      net_store(acc, bias + 2 * kCout, lds, half, [&](int q) { return to + map_chunk(p, q); });
     }
-    __syncthreads();
-    if (wid == 0) {  // head, in the order of head_fwd_kernel
-      const float* __restrict__ wh = a.params + kHeadOffset;
+    if (wid == 0 && i >= 2 && i <= count + 1) {  // layer 4: 4 x 4 x 32, in the head's order
+      f32x16 acc = {};
+      const int pos = lane & 31;
+      const int par = (int)(i & 1);
+      net_tile<8>(lds, kNetA3 + par * (8 * 8 * kCout / 8), w34, 0, lane, acc);
+      if (pos < 16)
+        net_store(acc, bias + 3 * kCout, lds, half, [&](int q) {
+          return kNetA4 + par * (4 * 4 * kCout / 8) + 4 * pos + q;
+        });
+    }
+    if (wid == 3 && i >= 3) {  // head, in the order of head_fwd_kernel
+      const bf16* x = reinterpret_cast<const bf16*>(
+          lds + kNetA4 + (int)((i - 3) & 1) * (4 * 4 * kCout / 8));
+      const float* wh = smem + kNetHead;
       float s0 = 0.0f, s1 = 0.0f;
-      for (int k = lane; k < kHeadIn; k += 64) {
-        const float x = (float)A4[k];
-        s0 = __builtin_fmaf(x, wh[k], s0);
-        s1 = __builtin_fmaf(x, wh[kHeadIn + k], s1);
+#pragma unroll
+      for (int k = 0; k < kHeadIn; k += 64) {
+        const float v = (float)x[k + lane];
+        s0 = __builtin_fmaf(v, wh[k + lane], s0);
+        s1 = __builtin_fmaf(v, wh[kHeadIn + k + lane], s1);
       }
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) {
@@ -421,11 +521,29 @@ __global__ __launch_bounds__(kNetThreads) void net_fused_kernel(const NetArgs a)
       }
       // every lane of the wave holds the same sums (the butterfly adds the
       // same two operands in every lane) and stores them
+      const int64_t pn = (int64_t)blockIdx.x + (i - 3) * gridDim.x;
       a.y[2 * pn] = s0 + wh[2 * kHeadIn];
       a.y[2 * pn + 1] = s1 + wh[2 * kHeadIn + 1];
     }
-    // the next pair's layer 1 overwrites layers 3-4 only after the barrier
-    // that follows its weight staging, which wave 0 reaches after the head
+    __syncthreads();
+    // ---- B
+    if (i + 1 < count) {
+#pragma unroll
+      for (int j = 0; j < kPre; ++j) reinterpret_cast<u32x4*>(lds)[feat_chunk(j)] = next[j];
+    }
+    if (i + 2 < count) {
+      const u32x4* src = map_of(i + 2);
+#pragma unroll
+      for (int j = 0; j < kPre; ++j) next[j] = src[tid + j * kNetThreads];
+    }
+    if (i < count) {  // layer 2: 16 x 16 x 32
+      f32x16 acc = {};
+      const int pos = 32 * wid + (lane & 31);
+      net_tile<32>(lds, kNetA1, w2, wid, lane, acc);
+      const int p = map_pixel<16>(pos >> 4, pos & 15);
+      net_store(acc, bias + kCout, lds, half, [&](int q) { return kNetA2 + map_chunk(p, q); });
+    }
+    __syncthreads();
   }
 }
 
