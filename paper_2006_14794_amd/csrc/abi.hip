@@ -583,16 +583,23 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   const sk::Batch bx = to_batch(X), by = to_batch(Y);
   if (X->offsets && sk::launch_plan(bx, px, stream) != hipSuccess) return SK_ERR_HIP;
   if (Y->offsets && sk::launch_plan(by, py, stream) != hipSuccess) return SK_ERR_HIP;
+  // pipelined bands: every pair joins the band-task queue (a short pair, or
+  // one without cells, is one task at the end of it) and there is no short
+  // class
+  const bool pipe = PL.pipe && tune.pair_bands != 1;
+  // Pairs of equal lengths are all of one class and need no order: no plan kernel
+  // and no launch for the other class (one pair of 32 points: 13.7 us the call against 19.4).
+  const bool plain = !pipe && !X->offsets && !Y->offsets;
+  int32_t* order = reinterpret_cast<int32_t*>(base + PL.order);
+  int32_t* counts = reinterpret_cast<int32_t*>(base + PL.counts);
   if (sk::launch_increments_xy(bx, X->offsets ? &px : nullptr, 1.0f, by,
                                Y->offsets ? &py : nullptr, 1.0f, dp, incx, incy, stream, rounding,
-                               o.rep) != hipSuccess)
+                               o.rep, counts + 2, plain ? 1 : 0) != hipSuccess)
     return SK_ERR_HIP;
   if (X->offsets && sk::launch_scale_plan(px, X->n_paths, o.rep, stream) != hipSuccess)
     return SK_ERR_HIP;
   if (Y->offsets && sk::launch_scale_plan(py, Y->n_paths, o.rep, stream) != hipSuccess)
     return SK_ERR_HIP;
-  int32_t* order = reinterpret_cast<int32_t*>(base + PL.order);
-  int32_t* counts = reinterpret_cast<int32_t*>(base + PL.counts);
   sk::PairPlanArgs pp{};
   pp.x_n = X->offsets ? px.n : nullptr;
   pp.x_len = Xr.len;
@@ -601,16 +608,12 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   pp.npairs = (int32_t)npairs;
   pp.gram_ny = gram ? Y->n_paths : 0;
   pp.lam = lam;
-  // pipelined bands: every pair joins the band-task queue (a short pair, or
-  // one without cells, is one task at the end of it) and there is no short
-  // class
-  const bool pipe = PL.pipe && tune.pair_bands != 1;
   pp.rows_lo = pipe ? 0 : PL.rows_lo;
   pp.rows_hi = PL.rows_hi;
   pp.order = order;
   pp.counts = counts;
   pp.counters = counts + 2;
-  if (sk::launch_pair_plan(pp, stream) != hipSuccess) return SK_ERR_HIP;
+  if (!plain && sk::launch_pair_plan(pp, stream) != hipSuccess) return SK_ERR_HIP;
 
   sk::PairArgs a{};
   a.incx = incx;
@@ -632,7 +635,14 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   a.count = counts;
   a.counter = counts + 2;
   hipError_t e = hipSuccess;
-  if (pipe) {
+  if (plain) {
+    a.order = nullptr;
+    a.count = nullptr;
+    a.n_pairs = (int32_t)npairs;
+    const int64_t M = (int64_t)((Xr.len < Yr.len ? Xr.len : Yr.len) - 1) << lam;
+    e = sk::launch_pairs(a, lam, M <= 64 * (int64_t)PL.rows_lo ? PL.rows_lo : PL.rows_hi, d,
+                         PL.slots, stream, tune.pair_blocks_per_cu);
+  } else if (pipe) {
     // long class: every band of a pair at once (pipelined band tasks)
     int32_t* task_base = reinterpret_cast<int32_t*>(base + PL.task_base);
     double* tbuf = reinterpret_cast<double*>(base + PL.tbuf);
@@ -662,7 +672,7 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   } else {
     e = sk::launch_pairs(a, lam, PL.rows_hi, d, PL.slots, stream, tune.pair_blocks_per_cu);
   }
-  if (e == hipSuccess && !pipe) {
+  if (e == hipSuccess && !pipe && !plain) {
     // the short class follows the long one in `order`; its offset (the long
     // class's count) is only known on the device, where the kernel reads it
     a.order = order;

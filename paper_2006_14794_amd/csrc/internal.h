@@ -144,10 +144,12 @@ struct PairArgs {
   const int64_t* y_start;
   int32_t x_len, y_len;
   double scale;             // 2^-(2 lam + 1)
-  const int32_t* order;     // pair ids, long class first, each class longest first
+  const int32_t* order;     // pair ids, long class first, each class longest first (nullptr:
+                            // pairs 0 .. n_pairs - 1, without a plan)
   const int32_t* order_base;  // device: offset of this class in `order` (nullptr: 0)
-  const int32_t* count;     // device: pairs in this class
-  int32_t* counter;         // device queue head (zeroed by the plan kernel)
+  const int32_t* count;     // device: pairs in this class (nullptr: n_pairs)
+  int32_t n_pairs;
+  int32_t* counter;         // device queue head (zeroed by an earlier kernel)
   double* bandbuf;          // per wave slot: band_stride doubles
   int64_t band_stride;
   float* out;               // out[pid]

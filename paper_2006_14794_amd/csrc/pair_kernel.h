@@ -36,8 +36,9 @@ __global__ __launch_bounds__(256) void pair_kernel(const PairArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t slot = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   double* __restrict__ bb = a.bandbuf + slot * a.band_stride;
-  const int32_t count = *a.count;
-  const int32_t* __restrict__ order = a.order + (a.order_base ? *a.order_base : 0);
+  const int32_t count = a.count ? *a.count : a.n_pairs;
+  const int32_t* __restrict__ order = a.order;
+  if (order && a.order_base) order += *a.order_base;
 
   // A wave's first pair is its slot's, so that as many pairs as SIMDs or fewer run
   // on as many SIMDs (workgroups go round the compute units) and not where a wave
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(256) void pair_kernel(const PairArgs a) {
     return (int32_t)(gridDim.x * (blockDim.x >> 6)) + __builtin_amdgcn_readlane(k, 0);
   };
   for (int32_t k = __builtin_amdgcn_readfirstlane((int32_t)slot); k < count; k = claim()) {
-    const int32_t pid = order[k];
+    const int32_t pid = order ? order[k] : k;
     const int64_t ix = a.gram_ny ? pid / a.gram_ny : pid;
     const int64_t iy = a.gram_ny ? pid - ix * a.gram_ny : pid;
     const int32_t mx = n_inc(a.x_n, a.x_len, ix), my = n_inc(a.y_n, a.y_len, iy);
