@@ -84,20 +84,22 @@ def grad_ops_per_cell(d: int, lam: int) -> float:
     equivalents: the forward cell and its share of the coarse inner product
     (as in sweep_ops_per_cell), the adjoint cell (two double FMAs), its
     coefficient-gradient product (one FMA) and the two increment contractions
-    (2 d double FMAs per coarse cell, shared by 4^lam fine cells).  The
-    recomputation of the forward values from checkpoints is not counted."""
+    (2 d double FMAs per coarse cell, shared by 4^lam fine cells).  Rebuilding
+    the forward values backwards is not counted."""
     return sweep_ops_per_cell(d, lam) + 3.0 + 2.0 * d / float(4 ** lam)
 
 
-# checkpoint traffic of the gradient kernel per fine cell (written once, read
-# once): R + 2^lam doubles per lane every C steps of R 2^lam cells, with R = 4
-# rows per lane and C the segment length (see grad_args.h)
-def grad_checkpoint_bytes_per_cell(d: int, lam: int) -> float:
-    R = 4
+# checkpoint traffic of the reversing gradient kernel per fine cell (written once,
+# read once): R + 2^lam + 1 doubles per lane every C ck steps of R 2^lam cells, with
+# R rows per lane, C the steps of a segment and ck the segments between two
+# checkpoints (see grad_args.h) at the workload's sizes
+def grad_checkpoint_bytes_per_cell(d: int, lam: int, cols: int) -> float:
     S = 1 << lam
-    floats_reg = 32 // (2 if lam == 0 else 1)
-    C = max(1, floats_reg // (R * S)) + max(1, 64 // (R * S))
-    return 2.0 * 8.0 * (R + S) / (R * S * C)
+    R = 8 if lam <= 2 and (8 >> lam) * d <= 16 else 4
+    C = {0: 32, 1: 24, 2: 16}.get(lam, 8)
+    segments = -(-(cols + 63) // C)
+    ck = 4 if segments >= 32 else segments // 8 if segments >= 16 else 1
+    return 2.0 * 8.0 * (R + S + 1) / (R * S * C * ck)
 
 
 # the files the Gram sweep kernel compiles from (its translation unit and headers)
@@ -282,10 +284,12 @@ def bench_mmd(args):
         "roofline": {"bound": "alu", "achieved": ops / t_b / 1e12, "peak": VALU_PEAK_TOPS,
                      "unit": "Tops/s", "frac": ops / t_b / 1e12 / VALU_PEAK_TOPS,
                      "traffic": None,
-                     "kernel": "grad_kernel: gradient of the cross term (64 x 64 pairs), events "
+                     "kernel": "grad_rev_kernel: gradient of the cross term (64 x 64 pairs), events "
                                "around the backward call (increments, gradient, point sums)",
                      "avg_launch_ms": t_b * 1e3, "ops_per_cell": grad_ops_per_cell(d, lam),
-                     "checkpoint_bytes_per_cell": grad_checkpoint_bytes_per_cell(d, lam)},
+                     # (two pairs per task: 2 (L - 1) columns)
+                     "checkpoint_bytes_per_cell":
+                         grad_checkpoint_bytes_per_cell(d, lam, 2 * (L - 1))},
     }
     if not args.no_cpu_baseline:
         import oracle
