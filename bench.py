@@ -95,7 +95,7 @@ def grad_ops_per_cell(d: int, lam: int) -> float:
 # checkpoints (see grad_args.h) at the workload's sizes
 def grad_checkpoint_bytes_per_cell(d: int, lam: int, cols: int) -> float:
     S = 1 << lam
-    R = 8 if lam <= 2 and (8 >> lam) * d <= 16 else 4
+    R = 8 if lam <= 2 and (8 >> lam) * d <= 24 else 4
     C = {0: 32, 1: 24, 2: 16}.get(lam, 8)
     segments = -(-(cols + 63) // C)
     ck = 4 if segments >= 32 else segments // 8 if segments >= 16 else 1

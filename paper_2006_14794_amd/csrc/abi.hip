@@ -476,7 +476,8 @@ GradPlan grad_plan(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, uint32_
     // Rows per lane and pairs per wave by the least modelled time of the
     // busiest SIMD: a task sweeps its bands in columns + lanes - 1 steps of
     // cost R + 3 each (a step's instructions that do not grow with R weigh
-    // like three rows), and a SIMD with a single wave issues at 0.7 of its rate.
+    // like three rows), and a SIMD with a single wave (or a kernel that leaves room
+    // for one) issues at 0.7 of its rate.
     const int64_t M = m << P.lam;
     const bool sym = (flags & SK_SYMMETRIC) != 0;
     const int64_t pairs = sym ? X0->n_paths * (X0->n_paths + 1) / 2 : X0->n_paths * Y0->n_paths;
@@ -492,7 +493,9 @@ GradPlan grad_plan(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, uint32_
         const int64_t tasks = (pairs + ng * run - 1) / (ng * run);
         const double task = (double)nb * (double)(run * n + 64 / ng - 1) * (R + 3);
         const int64_t per_simd = (tasks + kSimds - 1) / kSimds;
-        const double cost = (double)per_simd * task / (per_simd == 1 ? 0.7 : 1.0);
+        const double cost =
+            (double)per_simd * task /
+            (per_simd == 1 || sk::grad_rev_waves(R, P.lam, d) == 1 ? 0.7 : 1.0);
         if (best == 0.0 || cost < best) {
           best = cost;
           P.R = R;

@@ -100,10 +100,14 @@ __host__ __device__ inline GradSlot grad_slot_layout(int lam, int nb_max, int ns
 
 // ---- the reversing kernel (grad_rev_kernel.h) ----
 // Compiled rows per lane R: 4 always, 8 where the increments and accumulators
-// of the 8 / 2^lam coarse rows leave two waves per SIMD.
+// of the 8 / 2^lam coarse rows leave two waves per SIMD, or (more than 16 values)
+// one: half as many bands or lanes make up for it where a path fills them (30 x 30
+// paths of 400 points, d = 5, order 1: 929 us the call, 1293 with four rows; 64 x
+// 64 of 100, d = 7, order 2: 625 against 785; 100 x 100 of 120, d = 6, order 1 the
+// other way round: 953 against 860, and four rows run).
 __host__ __device__ constexpr bool grad_rev_fits(int R, int lam, int d) {
   if (R == 4) return true;
-  return R == 8 && lam <= 2 && (8 >> lam) * d <= 16;
+  return R == 8 && lam <= 2 && (8 >> lam) * d <= 24;
 }
 // Steps per segment of the staging.  Even, at most 32 (the pair-end masks).
 __host__ __device__ constexpr int grad_rev_segment(int lam) {
@@ -115,11 +119,15 @@ __host__ __device__ constexpr int grad_rev_segment(int lam) {
 __host__ __device__ constexpr int grad_rev_ck_every(int nseg_max) {
   return nseg_max >= 32 ? 4 : nseg_max >= 16 ? nseg_max / 8 : 1;
 }
-// Two waves per SIMD (256 registers) where the increments, their double
-// accumulators and the y-side sums leave room for the sweep's state; else one
-// or two, as the registers allow.
+// Two waves per SIMD (256 registers) where the increments and their double
+// accumulators leave room for the sweep's state; else one or two, as the
+// registers allow.
 __host__ __device__ constexpr int grad_rev_waves(int R, int lam, int d) {
-  return 3 * ((R >> lam) > 0 ? (R >> lam) : 1) * d + 4 * d <= 64 && lam < 3 ? 2 : 1;
+  return (R == 8 ? (8 >> lam) * d <= 16
+                 : 3 * ((R >> lam) > 0 ? (R >> lam) : 1) * d + 4 * d <= 64) &&
+                 lam < 3
+             ? 2
+             : 1;
 }
 __host__ __device__ constexpr int grad_rev_state_doubles(int R, int lam) {
   return R + (1 << lam) + 1;
