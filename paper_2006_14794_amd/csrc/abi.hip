@@ -611,7 +611,16 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   pp.npairs = (int32_t)npairs;
   pp.gram_ny = gram ? Y->n_paths : 0;
   pp.lam = lam;
-  pp.rows_lo = pipe ? 0 : PL.rows_lo;
+  // Up to one pair per SIMD (two where a step holds few cells): the classes are
+  // chains of steps whose time is mostly latency, so the short class joins the long
+  // one's launch, at its rows per lane, instead of waiting for it.  Ragged pairs, one
+  // launch against two: 77 of 11 to 77 points, order 0, 36.5 us the call against 54;
+  // 1000 of 20 to 250, order 3, 382 against 620; 2000 of 20 to 120, order 1, 91
+  // against 146.  With more pairs the issue rate counts and a short class of long
+  // columns would pay for the other's rows.
+  const bool one_class =
+      !pipe && npairs <= (PL.rows_hi << lam <= 32 ? 2 * kSimds : kSimds);
+  pp.rows_lo = pipe || one_class ? 0 : PL.rows_lo;
   pp.rows_hi = PL.rows_hi;
   pp.order = order;
   pp.counts = counts;
@@ -675,7 +684,7 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
   } else {
     e = sk::launch_pairs(a, lam, PL.rows_hi, d, PL.slots, stream, tune.pair_blocks_per_cu);
   }
-  if (e == hipSuccess && !pipe && !plain) {
+  if (e == hipSuccess && !pipe && !plain && !one_class) {
     // the short class follows the long one in `order`; its offset (the long
     // class's count) is only known on the device, where the kernel reads it
     a.order = order;
