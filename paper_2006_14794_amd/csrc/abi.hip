@@ -128,8 +128,13 @@ int64_t device_simds() {
 // one), 2 per fine cell, 2 (implicit: 8) per coarse row, 2^(lam + 1) DPP moves
 // and 16 more.  The busiest SIMD holds ceil(waves / SIMDs) waves, of which as
 // many run at once as the registers allow; with one, two or three it issues at
-// 0.73, 0.93 or 0.97 of its rate with four or more.  run: the tuned value or
-// 0; ties go to the shorter run.  (Both sides measured: sweep_fwd_kernel.h.)
+// 0.73, 0.88 or 0.97 of its rate with four or more (at 0.93 for two, 55 x 199 paths of
+// 80 and 95 points, d = 11, order 2, took runs of 6, 290 us, and now of 4, 274; a
+// symmetric 100 of 120 points, d = 3, order 2, runs of 3, 169, and single pairs now,
+// 155).  A wave alone takes at least 30 beside its step's work (48 x 40 paths of 100
+// points, d = 5, order 1: two waves of single pairs per SIMD 46 us, one of runs of
+// two 60).
+// run: the tuned value or 0; ties go to the shorter run.  (Both sides measured: sweep_fwd_kernel.h.)
 struct SweepShape {
   int R, ng;
   int64_t run;
@@ -171,8 +176,13 @@ SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t
     const int64_t waves = (runs + ng - 1) / ng;
     const int64_t per_simd = (waves + simds - 1) / simds;
     const int64_t at_once = per_simd < resident ? per_simd : resident;
-    const double step = kind == kLift && at_once == 1 && issue < 200.0 ? 200.0 : issue;
-    const double rate = at_once >= 4 ? 1.0 : at_once == 3 ? 0.97 : at_once == 2 ? 0.93 : kind == kLift ? 0.85 : 0.73;
+    const double rate = at_once >= 4   ? 1.0
+                        : at_once == 3 ? 0.97
+                        : at_once == 2 ? (kind == kLift ? 0.93 : 0.88)
+                                       : (kind == kLift ? 0.85 : 0.73);
+    double step = issue;
+    if (at_once == 1 && kind == kLift && step < 200.0) step = 200.0;
+    if (at_once == 1 && kind != kLift && step < 81.0) step = (step + 30.0) * rate;
     const double cost = (double)per_simd * (double)(k * n + gl - 1) * step / rate;
     if (best.R == 0 || cost < best_cost) {
       best = SweepShape{R, ng, k};
