@@ -114,8 +114,8 @@ __host__ __device__ constexpr int grad_rev_segment(int lam) {
   return lam == 0 ? 32 : lam == 1 ? 24 : lam == 2 ? 16 : 8;
 }
 // Segments between two checkpoints (R + 2^lam + 1 doubles per lane): at most
-// four, and at least eight checkpoints over the longest task's columns, which
-// bounds the region over which the rebuilt nodes drift.
+// four, and one in tasks of fewer than 16 segments, so that the rebuilt nodes
+// drift over at most an eighth of a task's columns, or one segment.
 __host__ __device__ constexpr int grad_rev_ck_every(int nseg_max) {
   return nseg_max >= 32 ? 4 : nseg_max >= 16 ? nseg_max / 8 : 1;
 }
