@@ -123,14 +123,14 @@ __device__ __forceinline__ void zero_counters(int32_t* zero, int n) {
   if (blockIdx.x == 0 && (int)threadIdx.x < n) zero[threadIdx.x] = 0;
 }
 
-// Workgroups [0, jx.n_paths) take the paths of jx, the rest those of jy.
+// Workgroups [0, jx.n_paths) take the paths of jx, the next jy.n_paths those of jy.
 __global__ __launch_bounds__(256) void increments_kernel(const IncJob jx, const IncJob jy,
                                                          int32_t* zero, int n_zero) {
   zero_counters(zero, n_zero);
   const int64_t b = blockIdx.x;
   if (b < jx.n_paths)
     increments_one(jx, b);
-  else
+  else if (b - jx.n_paths < jy.n_paths)
     increments_one(jy, b - jx.n_paths);
 }
 
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void increments4_kernel(const IncJob jx, const
   const int64_t b = blockIdx.x;
   if (b < jx.n_paths)
     increments4_one(jx, b);
-  else
+  else if (b - jx.n_paths < jy.n_paths)
     increments4_one(jy, b - jx.n_paths);
 }
 
@@ -317,8 +317,9 @@ hipError_t launch_increments_xy(const Batch& bx, const PathPlan* planx, float sc
                                 int rep, int32_t* zero, int n_zero) {
   const IncJob jx = make_job(bx, planx, scalex, dpad, incx, rounding, rep);
   const IncJob jy = make_job(by, plany, scaley, dpad, incy, rounding, rep);
-  const int64_t blocks = jx.n_paths + jy.n_paths;
-  if (blocks == 0) return hipSuccess;
+  int64_t blocks = jx.n_paths + jy.n_paths;
+  if (blocks == 0 && n_zero == 0) return hipSuccess;
+  if (blocks == 0) blocks = 1;  // one-point paths on both sides: the counters alone
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (four_wide(jx) && four_wide(jy))
     hipLaunchKernelGGL(increments4_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, jx, jy,

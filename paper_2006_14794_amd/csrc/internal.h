@@ -43,8 +43,8 @@ hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t stream);
 // that 16-bit format (the inner products then see 16-bit inputs, float32
 // sums).  With rep > 1 (a power of two) every increment fills rep
 // consecutive rows, each scale * (x_{p+1} - x_p) / rep: the batch refined rep
-// times, exactly (rows start[k] rep + p rep + j).  n_zero counters at `zero` are
-// zeroed by the same launch (some batch must have increments).
+// times, exactly (rows start[k] rep + p rep + j).  n_zero counters (at most 256)
+// at `zero` are zeroed by the same launch, also where neither batch has increments.
 enum { kRoundNone = 0, kRoundBf16 = 1, kRoundF16 = 2 };
 hipError_t launch_increments_xy(const Batch& bx, const PathPlan* planx, float scalex,
                                 const Batch& by, const PathPlan* plany, float scaley, int dpad,
