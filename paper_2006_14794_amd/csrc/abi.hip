@@ -445,7 +445,9 @@ struct GradPlan {
   int nb_max, nseg_max;
   int64_t cols_max;
   int32_t mrows, nrows;
-  int64_t slot_stride;  // doubles (the larger of the two kernels')
+  int64_t slot_stride;  // doubles (the larger of the kernels')
+  bool rev;             // the reversing kernel, then the recomputing one over its list;
+                        // else the recomputing kernel over all tasks
   int R, ng;            // the reversing kernel's rows per lane and pairs per wave
   int rev_nb_max, rev_nck_max, rev_ck_every;
   size_t order, counts, redo, scratch, partx, party, total;
@@ -465,6 +467,50 @@ int64_t choose_grad_run(int64_t nx, int64_t ny, bool sym, int32_t tuned) {
   return run;
 }
 
+// The layout of a plan whose kernel (rev, R, ng) and run are chosen.
+void grad_layout(GradPlan& P, const sk_paths* X0, const sk_paths* Y0) {
+  const sk_paths Xr = refined(X0, P.rep), Yr = refined(Y0, P.rep);
+  const int64_t m = P.mrows, n = P.nrows;
+  const int d = X0->dim;
+  P.runs_per_row = (Y0->n_paths + P.run - 1) / P.run;
+  P.n_tasks = X0->n_paths * P.runs_per_row;
+  P.slots = P.n_tasks < kGradSlots ? P.n_tasks : kGradSlots;
+  if (P.slots < 1) P.slots = 1;
+  const int64_t M = m << P.lam;
+  const int64_t band_rows = 64 * (int64_t)sk::kGradRows;
+  P.nb_max = (int)(M > 0 ? (M + band_rows - 1) / band_rows : 1);
+  P.cols_max = P.run * (n > 0 ? n : 1);
+  const int C = sk::grad_segment(P.lam, d);
+  P.nseg_max = (int)((P.cols_max + 63 + C - 1) / C);
+  P.slot_stride = sk::grad_slot_layout(P.lam, P.nb_max, P.nseg_max, P.cols_max).stride;
+  if (P.rev) {
+    const int64_t rev_rows = 64 / P.ng * (int64_t)P.R;
+    P.rev_nb_max = (int)(M > 0 ? (M + rev_rows - 1) / rev_rows : 1);
+    const int64_t rev_cols = P.ng > 1 ? (n > 0 ? n : 1) : P.cols_max;
+    const int RC = sk::grad_rev_segment(P.lam);
+    const int rev_nseg = (int)((rev_cols + 64 / P.ng - 1 + RC - 1) / RC);
+    P.rev_ck_every = sk::grad_rev_ck_every(rev_nseg);
+    P.rev_nck_max = (rev_nseg + P.rev_ck_every - 1) / P.rev_ck_every;
+    P.slot_stride = std::max(
+        P.slot_stride, sk::grad_rev_slot_layout(P.R, P.lam, P.rev_nb_max, P.rev_nck_max,
+                                                P.cols_max, P.ng > 1 ? 1 : P.run).stride);
+  }
+  size_t off = forward_ws(&Xr, &Yr);
+  P.order = off;
+  if (P.ragged) off += align256((size_t)(P.n_tasks > 0 ? P.n_tasks : 1) * sizeof(int32_t));
+  P.counts = off;
+  off += 256;  // the pair plan's counts and counters, the gradient queue heads
+  P.redo = off;
+  if (P.rev) off += align256((size_t)(P.n_tasks > 0 ? P.n_tasks : 1) * sizeof(int32_t));
+  P.scratch = off;
+  off += align256((size_t)P.slots * (size_t)P.slot_stride * sizeof(double));
+  P.partx = off;
+  off += align256((size_t)X0->n_paths * (size_t)P.runs_per_row * (size_t)m * d * sizeof(double));
+  P.party = off;
+  off += align256((size_t)X0->n_paths * Y0->n_paths * (size_t)n * d * sizeof(double));
+  P.total = off;
+}
+
 GradPlan grad_plan(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, uint32_t flags) {
   const Order o = split_order(lam0);
   const sk_paths Xr = refined(X0, o.rep), Yr = refined(Y0, o.rep);
@@ -478,84 +524,71 @@ GradPlan grad_plan(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, uint32_
   P.nrows = (int32_t)n;
   P.R = sk::kGradRows;
   P.ng = 1;
+  P.rev = true;
+  P.run = 1;
   if (P.ragged) {
-    P.run = 1;
-    P.runs_per_row = Y0->n_paths;
-  } else {
-    const sk_tune t = sk::tuning_for(SK_OP_GRAM_BACKWARD, X0, Y0, lam0, flags);
-    // Rows per lane and pairs per wave by the least modelled time of the
-    // busiest SIMD: a task sweeps its bands in columns + lanes - 1 steps of
-    // cost R + 3 each (a step's instructions that do not grow with R weigh
-    // like three rows), and a SIMD with a single wave (or a kernel that leaves room
-    // for one) issues at 0.7 of its rate.
-    const int64_t M = m << P.lam;
-    const bool sym = (flags & SK_SYMMETRIC) != 0;
-    const int64_t pairs = sym ? X0->n_paths * (X0->n_paths + 1) / 2 : X0->n_paths * Y0->n_paths;
-    double best = 0.0;
-    for (int R : {4, 8}) {
-      for (int ng : {1, 2, 4}) {
-        if (ng > 1 && (t.run > 0 || 64 / ng * (int64_t)R < M)) continue;
-        if (!sk::grad_rev_fn(P.lam, R, ng, d, true)) continue;
-        const int64_t run = ng > 1 || n < sk::grad_rev_segment(P.lam)
-                                ? 1
-                                : choose_grad_run(X0->n_paths, Y0->n_paths, sym, t.run);
-        const int64_t nb = (M + 64 / ng * (int64_t)R - 1) / (64 / ng * (int64_t)R);
-        const int64_t tasks = (pairs + ng * run - 1) / (ng * run);
-        const double task = (double)nb * (double)(run * n + 64 / ng - 1) * (R + 3);
-        const int64_t per_simd = (tasks + kSimds - 1) / kSimds;
-        const double cost =
-            (double)per_simd * task /
-            (per_simd == 1 || sk::grad_rev_waves(R, P.lam, d) == 1 ? 0.7 : 1.0);
-        if (best == 0.0 || cost < best) {
-          best = cost;
-          P.R = R;
-          P.ng = ng;
-        }
+    grad_layout(P, X0, Y0);
+    return P;
+  }
+  const sk_tune t = sk::tuning_for(SK_OP_GRAM_BACKWARD, X0, Y0, lam0, flags);
+  const int64_t M = m << P.lam;
+  const int64_t ny = Y0->n_paths > 0 ? Y0->n_paths : 1;
+  const bool sym = (flags & SK_SYMMETRIC) != 0;
+  const int64_t pairs = sym ? X0->n_paths * (X0->n_paths + 1) / 2 : X0->n_paths * Y0->n_paths;
+  // Kernel, rows per lane and pairs per wave by the least modelled time of the
+  // busiest SIMD: a task sweeps its bands in columns + lanes - 1 steps of
+  // cost R + 3 each (a step's instructions that do not grow with R weigh
+  // like three rows), the recomputing kernel's 1.4 of that, and 150 for what a task
+  // costs beside its steps; a SIMD with a single wave (or a kernel that leaves
+  // room for one) issues at 0.7 of its rate.
+  // Each double of a task's x-side part is written and read again: 16 bytes at
+  // 4.5 TB/s against the 47 ns of a cost unit.
+  auto cost = [&](const GradPlan& Q) {
+    const int64_t lanes = 64 / Q.ng, run = Q.ng > 1 ? 1 : Q.run;
+    const int64_t nb = (M + lanes * Q.R - 1) / (lanes * Q.R);
+    const int64_t tasks = (pairs + Q.ng * run - 1) / (Q.ng * run);
+    const double task =
+        (double)nb * (double)(run * n + lanes - 1) * (Q.R + 3) * (Q.rev ? 1.0 : 1.4) + 150.0;
+    const int64_t per_simd = (tasks + kSimds - 1) / kSimds;
+    const bool one = Q.rev ? sk::grad_rev_waves(Q.R, P.lam, d) == 1 : d > 4 || P.lam == 3;
+    return (double)per_simd * task / (per_simd == 1 || one ? 0.7 : 1.0) +
+           7.6e-5 * (double)(tasks * m * d);
+  };
+  // The recomputing kernel alone, with runs as long as the task count allows:
+  // what the others are measured against.  The reversing kernel takes one pair
+  // end per lane and segment, so its tasks are single pairs (or ng of them side by
+  // side) where y paths are shorter than a segment; many of those cost a
+  // wavefront's fill and an x-side part each (300 x 300 paths of 400 and 8 points,
+  // d = 5, order 0: 10.3 ms and 1.5 GB of workspace against 1.8 ms and 0.28 GB).
+  // A plan may take a quarter more workspace than this one, or 64 MB.
+  GradPlan base = P;
+  base.rev = false;
+  base.run = choose_grad_run(X0->n_paths, Y0->n_paths, sym, t.run);
+  grad_layout(base, X0, Y0);
+  const size_t most = base.total + std::max(base.total / 4, size_t(64) << 20);
+  const bool short_y = n < sk::grad_rev_segment(P.lam);
+  const bool keep_run = t.run > 0 && base.run > 1;  // a tuned run is obeyed
+  GradPlan best{};
+  double best_cost = 0.0;
+  for (int R : {4, 8}) {
+    for (int ng : {1, 2, 4}) {
+      if (ng > 1 && (t.run > 0 || 64 / ng * (int64_t)R < M)) continue;
+      if (ng == 1 && short_y && keep_run) continue;
+      if (!sk::grad_rev_fn(P.lam, R, ng, d, true)) continue;
+      GradPlan Q = P;
+      Q.R = R;
+      Q.ng = ng;
+      Q.run = ng > 1 ? (ng < ny ? ng : ny) : short_y ? 1 : base.run;
+      grad_layout(Q, X0, Y0);
+      if (Q.total > most) continue;
+      const double c = cost(Q);
+      if (best.run == 0 || c < best_cost) {
+        best = Q;
+        best_cost = c;
       }
     }
-    if (P.ng > 1)
-      P.run = P.ng < Y0->n_paths ? P.ng : (Y0->n_paths > 0 ? Y0->n_paths : 1);
-    else
-      P.run = choose_grad_run(X0->n_paths, Y0->n_paths, sym, t.run);
-    // the reversing kernel saves one pair end per lane and segment
-    if (P.ng == 1 && n < sk::grad_rev_segment(P.lam)) P.run = 1;
-    P.runs_per_row = (Y0->n_paths + P.run - 1) / P.run;
   }
-  P.n_tasks = X0->n_paths * P.runs_per_row;
-  P.slots = P.n_tasks < kGradSlots ? P.n_tasks : kGradSlots;
-  if (P.slots < 1) P.slots = 1;
-  const int64_t M = m << P.lam;
-  const int64_t band_rows = 64 * (int64_t)sk::kGradRows;
-  P.nb_max = (int)(M > 0 ? (M + band_rows - 1) / band_rows : 1);
-  P.cols_max = P.run * (n > 0 ? n : 1);
-  const int C = sk::grad_segment(P.lam, d);
-  P.nseg_max = (int)((P.cols_max + 63 + C - 1) / C);
-  const int64_t rev_rows = 64 / P.ng * (int64_t)P.R;
-  P.rev_nb_max = (int)(M > 0 ? (M + rev_rows - 1) / rev_rows : 1);
-  const int64_t rev_cols = P.ng > 1 ? (n > 0 ? n : 1) : P.cols_max;
-  const int RC = sk::grad_rev_segment(P.lam);
-  const int rev_nseg = (int)((rev_cols + 64 / P.ng - 1 + RC - 1) / RC);
-  P.rev_ck_every = sk::grad_rev_ck_every(rev_nseg);
-  P.rev_nck_max = (rev_nseg + P.rev_ck_every - 1) / P.rev_ck_every;
-  P.slot_stride = std::max(
-      sk::grad_slot_layout(P.lam, P.nb_max, P.nseg_max, P.cols_max).stride,
-      sk::grad_rev_slot_layout(P.R, P.lam, P.rev_nb_max, P.rev_nck_max, P.cols_max,
-                               P.ng > 1 ? 1 : P.run).stride);
-  size_t off = forward_ws(&Xr, &Yr);
-  P.order = off;
-  if (P.ragged) off += align256((size_t)(P.n_tasks > 0 ? P.n_tasks : 1) * sizeof(int32_t));
-  P.counts = off;
-  off += 256;  // the pair plan's counts and counters, the gradient queue heads
-  P.redo = off;
-  off += align256((size_t)(P.n_tasks > 0 ? P.n_tasks : 1) * sizeof(int32_t));
-  P.scratch = off;
-  off += align256((size_t)P.slots * (size_t)P.slot_stride * sizeof(double));
-  P.partx = off;
-  off += align256((size_t)X0->n_paths * (size_t)P.runs_per_row * (size_t)m * d * sizeof(double));
-  P.party = off;
-  off += align256((size_t)X0->n_paths * Y0->n_paths * (size_t)n * d * sizeof(double));
-  P.total = off;
-  return P;
+  return best.run == 0 || (short_y && cost(base) < best_cost) ? base : best;
 }
 
 int rounding_of(uint32_t flags) {
@@ -1583,16 +1616,20 @@ static sk_status gram_backward(const sk_paths* X, const sk_paths* Y, int32_t dya
   ga.part_y = ys ? reinterpret_cast<double*>(base + P.party) : nullptr;
   ga.mrows = P.mrows;
   ga.nrows = P.nrows;
-  // the reversing kernel over every task, then the recomputing one over the
-  // tasks it listed
-  ga.redo = reinterpret_cast<int32_t*>(base + P.redo);
-  ga.redo_count = counts + 6;
-  sk::GradArgs gf = ga;
-  gf.nb_max = P.rev_nb_max;
-  gf.ck_every = P.rev_ck_every;
-  gf.nck_max = P.rev_nck_max;
-  ga.counter = counts + 5;
-  if (sk::launch_grad(gf, ga, P.R, P.ng, lam, d, ys, P.slots, st) != hipSuccess) return SK_ERR_HIP;
+  if (P.rev) {
+    // the reversing kernel over every task, then the recomputing one over the
+    // tasks it listed
+    ga.redo = reinterpret_cast<int32_t*>(base + P.redo);
+    ga.redo_count = counts + 6;
+    sk::GradArgs gf = ga;
+    gf.nb_max = P.rev_nb_max;
+    gf.ck_every = P.rev_ck_every;
+    gf.nck_max = P.rev_nck_max;
+    ga.counter = counts + 5;
+    if (sk::launch_grad_rev(gf, P.R, P.ng, lam, d, ys, P.slots, st) != hipSuccess)
+      return SK_ERR_HIP;
+  }
+  if (sk::launch_grad(ga, lam, d, ys, P.slots, st) != hipSuccess) return SK_ERR_HIP;
 
   // the parts of a refined increment are the increment over rep: their
   // gradients sum, times 1 / rep, to the increment's

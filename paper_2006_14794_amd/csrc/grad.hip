@@ -121,18 +121,26 @@ __global__ __launch_bounds__(256) void grad_points_kernel(const GradPointArgs a)
 
 bool grad_supported(int lam, int d) { return grad_fn(lam, d, true) != nullptr; }
 
-hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng, int lam, int d,
-                       bool ys, int64_t slots, hipStream_t stream) {
-  auto f = reinterpret_cast<void (*)(const GradArgs)>(grad_rev_fn(lam, R, ng, d, ys));
-  auto g = reinterpret_cast<void (*)(const GradArgs)>(grad_fn(lam, d, ys));
-  if (!f || !g) return hipErrorInvalidValue;
-  if (fast.n_tasks <= 0 || slots <= 0) return hipSuccess;
+namespace {
+hipError_t launch_tasks(void* fn, const GradArgs& a, int64_t slots, hipStream_t stream) {
+  auto f = reinterpret_cast<void (*)(const GradArgs)>(fn);
+  if (!f) return hipErrorInvalidValue;
+  if (a.n_tasks <= 0 || slots <= 0) return hipSuccess;
   // one wave per workgroup: slot = workgroup; every slot's scratch is its own,
   // so any number of them may be resident at once
-  hipLaunchKernelGGL(f, dim3((unsigned)slots), dim3(64), 0, stream, fast);
-  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  hipLaunchKernelGGL(g, dim3((unsigned)slots), dim3(64), 0, stream, redo);
+  hipLaunchKernelGGL(f, dim3((unsigned)slots), dim3(64), 0, stream, a);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_grad_rev(const GradArgs& a, int R, int ng, int lam, int d, bool ys,
+                           int64_t slots, hipStream_t stream) {
+  return launch_tasks(grad_rev_fn(lam, R, ng, d, ys), a, slots, stream);
+}
+
+hipError_t launch_grad(const GradArgs& a, int lam, int d, bool ys, int64_t slots,
+                       hipStream_t stream) {
+  return launch_tasks(grad_fn(lam, d, ys), a, slots, stream);
 }
 
 hipError_t launch_grad_points(const GradPointArgs& a, hipStream_t stream) {

@@ -93,14 +93,17 @@ hipError_t launch_lifted(const SweepArgs& a, int lam, int rows_per_lane, int ng,
 
 // Gradient of weighted Gram entries (grad_rev_kernel.h, grad_kernel.h,
 // grad.hip): persistent waves over the tasks, `slots` of them, each with its
-// own scratch slot.  `fast` runs every task on the reversing kernel with R rows
-// per lane and ng pairs per wave; `redo` then runs the tasks of its list on
-// the recomputing one.  The kGradCounters queue heads at fast.counter (fast's,
-// redo's, the list's length) must be zero (launch_increments_xy).  ys: form the
-// y-side gradients (part_y), else the x side only.
+// own scratch slot.  launch_grad_rev runs every task on the reversing kernel with
+// R rows per lane and ng pairs per wave; launch_grad those of its list
+// (a.redo) on the recomputing one, or every task where there is no list.  The
+// kGradCounters queue heads of a call (the reversing kernel's, the other's, the
+// list's length) must be zero (launch_increments_xy).  ys: form the y-side
+// gradients (part_y), else the x side only.
 constexpr int kGradCounters = 3;
-hipError_t launch_grad(const GradArgs& fast, const GradArgs& redo, int R, int ng, int lam, int dim,
-                       bool ys, int64_t slots, hipStream_t stream);
+hipError_t launch_grad_rev(const GradArgs& a, int R, int ng, int lam, int dim, bool ys,
+                           int64_t slots, hipStream_t stream);
+hipError_t launch_grad(const GradArgs& a, int lam, int dim, bool ys, int64_t slots,
+                       hipStream_t stream);
 // The reversing kernel at R rows per lane and ng pairs per wave; nullptr when
 // it is not compiled.
 void* grad_rev_fn(int lam, int R, int ng, int d, bool ys);

@@ -1,0 +1,27 @@
+"""Workspace sizes that callers depend on (no GPU: sizes only)."""
+import ctypes
+
+import pytest
+
+from paper_2006_14794_amd import _lib
+from paper_2006_14794_amd._lib import SkPaths
+
+FAKE = 0x10000
+
+
+def need(op, nx, lx, ny, ly, d, lam, flags=0):
+    X, Y = SkPaths(FAKE, None, nx, lx, d), SkPaths(FAKE * 2, None, ny, ly, d)
+    return _lib.load().sigkernel_workspace_bytes(op, ctypes.byref(X), ctypes.byref(Y), lam, flags)
+
+
+# Many pairs with short y paths: the x-side parts are one per task, so tasks of
+# single pairs would take tens of times the space of runs.  Bound: the plan with runs
+# of up to 64 pairs, a quarter of it more and 64 MB.
+@pytest.mark.parametrize("lam,d,nx,ny,lx,ly,bytes_", [
+    (0, 3, 557, 1841, 1504, 2, 819419904), (2, 13, 630, 316, 2102, 2, 6752291072),
+    (2, 2, 2377, 2484, 656, 12, 14332197376), (0, 5, 300, 300, 400, 8, 276540160),
+    (1, 4, 64, 1000, 100, 10, 229324800), (1, 5, 256, 256, 200, 20, 840188160)])
+def test_gradient_of_many_short_y_paths(lam, d, nx, ny, lx, ly, bytes_):
+    """bytes_: the recomputing kernel's plan, runs of up to 64 pairs per task."""
+    got = need(_lib.SK_OP_GRAM_BACKWARD, nx, lx, ny, ly, d, lam)
+    assert got <= 1.25 * bytes_ + (64 << 20)
