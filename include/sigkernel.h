@@ -139,8 +139,10 @@ sk_status sigkernel_gram(const sk_paths *X, const sk_paths *Y, int32_t dyadic_or
  * that forbid allocation.  The workspace is a static device array of
  * sigkernel_gram_noalloc_max_bytes() bytes (64 MiB) inside the library, one
  * per GPU, held until the process ends; the call allocates nothing.
- *  - A problem whose workspace (sigkernel_workspace_bytes(SK_OP_GRAM, ...))
- *    exceeds that size gives SK_ERR_WORKSPACE, with nothing enqueued.
+ *  - A problem that needs more than that size gives SK_ERR_WORKSPACE, with
+ *    nothing enqueued.  (Few tall paths run in a smaller layout than the one
+ *    sigkernel_workspace_bytes(SK_OP_GRAM, ...) asks for where that one does
+ *    not fit; the values are the same.)
  *  - stream must belong to the current device; the array's address on the
  *    device is looked up on the first call there (SK_ERR_HIP on failure).
  *  - Every call on one GPU uses the same array: calls that overlap on one

@@ -264,74 +264,19 @@ struct BandChoice {
   double cycles;
 };
 
-BandChoice choose_bands(const sk_paths* X, const sk_paths* Y, int32_t lam0, int64_t npairs,
-                        size_t inc_budget) {
-  BandChoice best{0, 0, 0.0};
-  const int64_t mx = X->len - 1, my = Y->len - 1;
-  const int64_t rows = (mx < my ? mx : my) << lam0;
-  const int d = X->dim;
-  for (int k = lam0 < kMaxKernelOrder ? lam0 : kMaxKernelOrder; k >= 0; --k) {
-    const int64_t rep = int64_t(1) << (lam0 - k), S = int64_t(1) << k;
-    const int64_t cols = (mx > my ? mx : my) * rep;
-    const size_t inc = ((size_t)X->n_paths * mx + (size_t)Y->n_paths * my) * (size_t)rep *
-                       (size_t)sk::padded_dim(d) * sizeof(float);
-    if (k < kMaxKernelOrder && k < lam0 && inc > inc_budget) break;
-    for (int R = 1; R <= sk::kMaxRowsPerLane; R *= 2) {
-      if (!sk::sweep_fn(sk::kKernelPairBandFull, k, R, d)) continue;
-      const int64_t nb = (rows + 64 * (int64_t)R - 1) / (64 * (int64_t)R);
-      const int64_t stride = (cols + 1 + 2 * sk::kStreamPad) << k;
-      if (nb < 2 || nb * npairs > INT32_MAX ||
-          (size_t)(nb * npairs) * (size_t)stride * sizeof(double) > kPipeCapBytes)
-        continue;
-      const double cell = 8.8 * (double)(R * S) + 2.8 * d * (double)(R >= S ? R / S : 1);
-      const double chain =
-          (double)(cols + 63 + (nb - 1) * 100) * (cell + 350.0 + 20.0 * (double)S);
-      const double issue = (double)(nb * npairs) * (double)(cols + 63) * (cell + 200.0) / kSimds;
-      const double cycles = chain > issue ? chain : issue;
-      if (best.R == 0 || cycles < best.cycles) best = BandChoice{k, R, cycles};
-    }
-  }
-  return best;
-}
-// Increments of a refined batch that the choice above may add to a workspace.
-constexpr size_t kBandIncBytes = size_t(64) << 20;
-
-// fixed_order: the caller launches the pair kernel itself, at order lam0.
-PairLayout pair_layout(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, bool gram,
-                       bool fixed_order = false) {
+// The layout at kernel order and refinement o; force_rows: bands of 64 force_rows
+// rows (0: as many rows per lane as the longest pair fills); bands: pipelined where
+// a grid needs several and their slots fit kPipeCapBytes.
+PairLayout pair_layout_at(const sk_paths* X0, const sk_paths* Y0, Order o, bool gram,
+                          int force_rows, bool bands = true) {
   PairLayout L{};
-  L.o = split_order(lam0);
+  L.o = o;
   const int64_t npairs = gram ? X0->n_paths * Y0->n_paths : X0->n_paths;
   const int d = X0->dim;
-  int force_rows = 0;
-  const int64_t least = (X0->len < Y0->len ? X0->len : Y0->len) - 1;
-  if (!fixed_order && !X0->offsets && !Y0->offsets && least << lam0 > 64) {
-    // against one wave per pair: its rows in one band of pair_kernel (about 600
-    // cycles of latencies a step) and some 15 us less for the launches
-    const int64_t longer = (X0->len > Y0->len ? X0->len : Y0->len) - 1;
-    const int64_t fine = least << lam0;
-    int R = 1;
-    while (R < sk::kMaxRowsPerLane && 64 * (int64_t)R < fine) R *= 2;
-    const bool one_band = 64 * (int64_t)R >= fine && sk::sweep_fn(sk::kKernelPair, L.o.k, R, d);
-    const BandChoice c = choose_bands(X0, Y0, lam0, npairs, kBandIncBytes);
-    double single = 0.0;
-    if (one_band) {
-      const double cell = 8.8 * (double)(R << L.o.k) +
-                          2.8 * d * (double)((R >> L.o.k) > 0 ? R >> L.o.k : 1);
-      const double steps = (double)(longer * L.o.rep + 63);
-      const double chain = steps * (cell + 600.0);
-      const double issue = (double)npairs * steps * (cell + 200.0) / kSimds;
-      single = (chain > issue ? chain : issue) * 0.9;
-    }
-    if (c.R > 0 && (!one_band || c.cycles + 36e3 < single)) {
-      L.o = Order{c.k, 1 << (lam0 - c.k)};
-      force_rows = c.R;
-    }
-  }
-  const sk_paths Xr = refined(X0, L.o.rep), Yr = refined(Y0, L.o.rep);
+  const sk_paths Xr = refined(X0, o.rep), Yr = refined(Y0, o.rep);
   const sk_paths* X = &Xr;
   const sk_paths* Y = &Yr;
-  const int32_t lam = L.o.k;
+  const int32_t lam = o.k;
   // rows of the longest possible pair (its shorter path on the rows)
   const int64_t shorter = (X->len < Y->len ? X->len : Y->len) - 1;
   const int64_t rows = (shorter < 1 ? 1 : shorter) << lam;
@@ -350,7 +295,7 @@ PairLayout pair_layout(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, boo
   L.band_stride = (longer + 2 * sk::kStreamPad) << lam;
   const int64_t nb_max = L.rows_hi ? (rows + 64 * (int64_t)L.rows_hi - 1) / (64 * L.rows_hi) : 1;
   L.tasks_max = npairs * nb_max;
-  L.pipe = L.rows_hi > 0 && nb_max > 1 && npairs <= INT32_MAX &&
+  L.pipe = bands && L.rows_hi > 0 && nb_max > 1 && npairs <= INT32_MAX &&
            (size_t)L.tasks_max * (size_t)L.band_stride * sizeof(double) <= kPipeCapBytes;
   size_t off = forward_ws(X, Y);
   L.order = off;
@@ -368,6 +313,74 @@ PairLayout pair_layout(const sk_paths* X0, const sk_paths* Y0, int32_t lam0, boo
   }
   L.total = off;
   return L;
+}
+
+// Increments of a refined batch that the choice below may add to a workspace.
+constexpr size_t kBandIncBytes = size_t(64) << 20;
+
+// budget: the workspace at hand; a choice that needs more is none.
+BandChoice choose_bands(const sk_paths* X, const sk_paths* Y, int32_t lam0, bool gram,
+                        size_t budget) {
+  BandChoice best{0, 0, 0.0};
+  const int64_t npairs = gram ? X->n_paths * Y->n_paths : X->n_paths;
+  const int64_t mx = X->len - 1, my = Y->len - 1;
+  const int64_t rows = (mx < my ? mx : my) << lam0;
+  const int d = X->dim;
+  for (int k = lam0 < kMaxKernelOrder ? lam0 : kMaxKernelOrder; k >= 0; --k) {
+    const int64_t rep = int64_t(1) << (lam0 - k), S = int64_t(1) << k;
+    const int64_t cols = (mx > my ? mx : my) * rep;
+    const size_t inc = ((size_t)X->n_paths * mx + (size_t)Y->n_paths * my) * (size_t)rep *
+                       (size_t)sk::padded_dim(d) * sizeof(float);
+    if (k < kMaxKernelOrder && k < lam0 && inc > kBandIncBytes) break;
+    for (int R = 1; R <= sk::kMaxRowsPerLane; R *= 2) {
+      if (!sk::sweep_fn(sk::kKernelPairBandFull, k, R, d)) continue;
+      const int64_t nb = (rows + 64 * (int64_t)R - 1) / (64 * (int64_t)R);
+      const int64_t stride = (cols + 1 + 2 * sk::kStreamPad) << k;
+      if (nb < 2 || nb * npairs > INT32_MAX ||
+          (size_t)(nb * npairs) * (size_t)stride * sizeof(double) > kPipeCapBytes ||
+          pair_layout_at(X, Y, Order{k, (int32_t)rep}, gram, R).total > budget)
+        continue;
+      const double cell = 8.8 * (double)(R * S) + 2.8 * d * (double)(R >= S ? R / S : 1);
+      const double chain =
+          (double)(cols + 63 + (nb - 1) * 100) * (cell + 350.0 + 20.0 * (double)S);
+      const double issue = (double)(nb * npairs) * (double)(cols + 63) * (cell + 200.0) / kSimds;
+      const double cycles = chain > issue ? chain : issue;
+      if (best.R == 0 || cycles < best.cycles) best = BandChoice{k, R, cycles};
+    }
+  }
+  return best;
+}
+
+// The fastest layout of at most `budget` bytes; where none is as small, the
+// smallest (one wave per pair, or bands at the largest height).
+PairLayout pair_layout(const sk_paths* X, const sk_paths* Y, int32_t lam0, bool gram,
+                       size_t budget = SIZE_MAX) {
+  const Order o = split_order(lam0);
+  const int64_t least = (X->len < Y->len ? X->len : Y->len) - 1;
+  if (!X->offsets && !Y->offsets && least << lam0 > 64) {
+    // against one wave per pair: its rows in one band of pair_kernel (about 600
+    // cycles of latencies a step) and some 15 us less for the launches
+    const int64_t npairs = gram ? X->n_paths * Y->n_paths : X->n_paths;
+    const int d = X->dim;
+    const int64_t longer = (X->len > Y->len ? X->len : Y->len) - 1;
+    const int64_t fine = least << lam0;
+    int R = 1;
+    while (R < sk::kMaxRowsPerLane && 64 * (int64_t)R < fine) R *= 2;
+    const bool one_band = 64 * (int64_t)R >= fine && sk::sweep_fn(sk::kKernelPair, o.k, R, d);
+    const BandChoice c = choose_bands(X, Y, lam0, gram, budget);
+    double single = 0.0;
+    if (one_band) {
+      const double cell =
+          8.8 * (double)(R << o.k) + 2.8 * d * (double)((R >> o.k) > 0 ? R >> o.k : 1);
+      const double steps = (double)(longer * o.rep + 63);
+      const double chain = steps * (cell + 600.0);
+      const double issue = (double)npairs * steps * (cell + 200.0) / kSimds;
+      single = (chain > issue ? chain : issue) * 0.9;
+    }
+    if (c.R > 0 && (!one_band || c.cycles + 36e3 < single))
+      return pair_layout_at(X, Y, Order{c.k, 1 << (lam0 - c.k)}, gram, c.R);
+  }
+  return pair_layout_at(X, Y, o, gram, 0);
 }
 
 // Channels beyond which the fused sweeps are not compiled: wider batches run
@@ -419,15 +432,15 @@ CoefPlan coef_plan(const sk_paths* X, const sk_paths* Y, int32_t lam0, int mode)
 
 // Workspace of a Gram call: the one-wave sweep's layout or, for x paths too
 // tall for it, the persistent pair kernel's; the coefficient sweep's for
-// batches wider than the fused sweeps.
-size_t gram_ws(const sk_paths* X, const sk_paths* Y, int32_t lam) {
+// batches wider than the fused sweeps.  budget: of the layouts that serve, the
+// fastest of at most this size (or the smallest, where none is).
+size_t gram_ws(const sk_paths* X, const sk_paths* Y, int32_t lam, size_t budget = SIZE_MAX) {
   if (X->dim > kMaxFusedDim && X->dim == Y->dim) return coef_plan(X, Y, lam, 1).total;
   const Order o = split_order(lam);
   const sk_paths Xr = refined(X, o.rep), Yr = refined(Y, o.rep);
-  const size_t f = forward_ws(&Xr, &Yr);
-  if (X->dim != Y->dim) return f;
-  const size_t g = pair_layout(X, Y, lam, true).total;
-  return f > g ? f : g;
+  if (X->dim != Y->dim || sk::forward_takes((int64_t)(Xr.len - 1) << o.k, o.k, X->dim))
+    return forward_ws(&Xr, &Yr);
+  return pair_layout(X, Y, lam, true, budget).total;
 }
 
 // Gram gradient workspace: the forward layout (increments, and the plans of
@@ -610,7 +623,11 @@ sk_status run_pairs(const sk_paths* X, const sk_paths* Y, int32_t lam0, float* o
                     const sk_tune& tune, bool implicit) {
   const int d = X->dim;
   const int dp = sk::padded_dim(d);
-  const PairLayout PL = pair_layout(X, Y, lam0, gram);
+  PairLayout PL = pair_layout(X, Y, lam0, gram, ws_bytes);
+  if (tune.pair_bands == 1) {  // one wave per pair: in as few bands as it can
+    const PairLayout P1 = pair_layout_at(X, Y, split_order(lam0), gram, 0, false);
+    if (P1.total <= ws_bytes) PL = P1;
+  }
   const int64_t npairs = gram ? X->n_paths * Y->n_paths : X->n_paths;
   if (npairs > INT32_MAX) return SK_ERR_UNSUPPORTED;
   if (PL.rows_hi == 0) return SK_ERR_UNSUPPORTED;
@@ -1017,7 +1034,7 @@ struct PredictLayout {
 
 PredictLayout predict_layout(const sk_paths* X, const sk_paths* Y, int32_t lam) {
   PredictLayout L{};
-  L.pl = pair_layout(X, Y, lam, false, true);
+  L.pl = pair_layout_at(X, Y, split_order(lam), false, 0);
   const size_t n = (size_t)X->n_paths;
   size_t off = L.pl.total;
   L.wb = off;
@@ -1305,7 +1322,8 @@ sk_status sigkernel_gram_noalloc(const sk_paths* X, const sk_paths* Y, int32_t d
           flags, SK_SYMMETRIC | SK_NO_DIAG | SK_GRAM_BF16 | SK_GRAM_F16 | SK_IMPLICIT))
     return f;
   if (X->n_paths == 0 || Y->n_paths == 0) return SK_OK;
-  if (gram_ws(X, Y, dyadic_order) > kNoAllocScratchBytes) return SK_ERR_WORKSPACE;
+  if (gram_ws(X, Y, dyadic_order, kNoAllocScratchBytes) > kNoAllocScratchBytes)
+    return SK_ERR_WORKSPACE;
   void* ws = scratch_address();
   if (!ws) return SK_ERR_HIP;
   return sigkernel_gram(X, Y, dyadic_order, flags, K, ws, kNoAllocScratchBytes, stream);

@@ -25,3 +25,13 @@ def test_gradient_of_many_short_y_paths(lam, d, nx, ny, lx, ly, bytes_):
     """bytes_: the recomputing kernel's plan, runs of up to 64 pairs per task."""
     got = need(_lib.SK_OP_GRAM_BACKWARD, nx, lx, ny, ly, d, lam)
     assert got <= 1.25 * bytes_ + (64 << 20)
+
+
+# x paths within one wave's rows: the Gram needs its increments and their padding,
+# not the layout of the persistent pair kernel (pairs of long paths, in bands)
+@pytest.mark.parametrize("lam,d,nx,ny,lx,ly", [(1, 6, 100, 100, 300, 300), (5, 1, 129, 129, 33, 94),
+                                               (4, 2, 12, 81, 100, 2700), (0, 8, 128, 128, 256, 256)])
+def test_gram_of_one_wave_paths(lam, d, nx, ny, lx, ly):
+    rep = 1 << max(lam - 3, 0)
+    rows = (nx * (lx - 1) + ny * (ly - 1)) * rep + 4 * 128
+    assert need(_lib.SK_OP_GRAM, nx, lx, ny, ly, d, lam) <= rows * ((d + 3) // 4 * 4) * 4 + 4096
