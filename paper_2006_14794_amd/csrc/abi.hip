@@ -134,7 +134,8 @@ int64_t device_simds() {
 // 155).  A wave alone takes at least 30 beside its step's work (48 x 40 paths of 100
 // points, d = 5, order 1: two waves of single pairs per SIMD 46 us, one of runs of
 // two 60).
-// run: the tuned value or 0; ties go to the shorter run.  (Both sides measured: sweep_fwd_kernel.h.)
+// run: the tuned value or 0; ties go to the shorter run.  simds: of the device, or
+// kSimds where a workspace size depends on the shape.  (Both sides measured: sweep_fwd_kernel.h.)
 struct SweepShape {
   int R, ng;
   int64_t run;
@@ -150,8 +151,7 @@ struct SweepShape {
 enum SweepKind { kPlain, kCoef, kLift };
 SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t n, int lam,
                               int d, bool implicit, bool sym, bool no_diag, int32_t run,
-                              SweepKind kind = kPlain) {
-  const int64_t simds = device_simds();
+                              int64_t simds, SweepKind kind = kPlain) {
   const int64_t M = fine_rows < 1 ? 1 : fine_rows;
   const int64_t cap = ny < 64 ? (ny < 1 ? 1 : ny) : 64;
   const int64_t tuned = run < ny ? run : (ny > 0 ? ny : 1);
@@ -413,7 +413,7 @@ CoefPlan coef_plan(const sk_paths* X, const sk_paths* Y, int32_t lam0, int mode)
   const int64_t ny = mode == 0 ? 1 : Y->n_paths;
   const SweepShape sh = choose_sweep_shape(
       X->n_paths, ny, fine_rows, Yr.len > 1 ? Yr.len - 1 : 1, o.k, X->dim, false, false, false,
-      mode == 0 || Y->offsets ? 1 : 0, kCoef);
+      mode == 0 || Y->offsets ? 1 : 0, kSimds, kCoef);
   P.R = sh.R;
   P.ng = sh.ng;
   if (P.R == 0) return P;
@@ -937,7 +937,7 @@ sk_status run_forward(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32
   a.out_ld = Y->n_paths;
   const SweepShape sh =
       choose_sweep_shape(X->n_paths, Y->n_paths, fine_rows, Yr.len - 1, lam, d, implicit,
-                         mode == 2, a.no_diag != 0, Y->offsets ? 1 : tune.run);
+                         mode == 2, a.no_diag != 0, Y->offsets ? 1 : tune.run, device_simds());
   if (sh.R == 0) return SK_ERR_UNSUPPORTED;
   a.run = (int32_t)sh.run;
   a.runs_per_row = (Y->n_paths + a.run - 1) / a.run;
@@ -1172,7 +1172,7 @@ sk_status run_lifted(const sk_paths* X, const sk_paths* Y, int32_t lam, uint32_t
   const int64_t ny_ = mode == 0 ? 1 : Y->n_paths;
   const SweepShape sh = choose_sweep_shape(X->n_paths, ny_, fine_rows, Y->len, lam, d,
                                            a.implicit != 0, mode == 2, a.no_diag != 0,
-                                           mode == 0 || Y->offsets ? 1 : 0, kLift);
+                                           mode == 0 || Y->offsets ? 1 : 0, device_simds(), kLift);
   if (sh.R == 0) return SK_ERR_UNSUPPORTED;
   a.run = (int32_t)sh.run;
   a.runs_per_row = mode == 0 ? 1 : (Y->n_paths + a.run - 1) / a.run;
