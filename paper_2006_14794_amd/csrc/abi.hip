@@ -417,7 +417,9 @@ CoefPlan coef_plan(const sk_paths* X, const sk_paths* Y, int32_t lam0, int mode)
   P.R = sh.R;
   P.ng = sh.ng;
   if (P.R == 0) return P;
-  P.run = (int32_t)sh.run;
+  // a run's columns: within the tiles of a grid's second dimension
+  const int64_t most = std::max<int64_t>(1, sk::kCoefMaxCols / (Yr.len > 1 ? Yr.len - 1 : 1));
+  P.run = (int32_t)std::min(sh.run, most);
   P.runs_per_row = mode == 0 ? 1 : (ny + P.run - 1) / P.run;
   P.runs = X->n_paths * P.runs_per_row;
   const int64_t cols = (int64_t)P.run * (Yr.len > 1 ? Yr.len - 1 : 1);
@@ -846,7 +848,7 @@ sk_status run_coef(const sk_paths* X, const sk_paths* Y, int32_t lam0, uint32_t 
     // workgroups over whole rows where their columns are one stream (and few
     // enough tiles for a grid's second dimension)
     c.by_row = mode != 0 && !Y->offsets && P.rep == 1 &&
-               Y->n_paths * (int64_t)(Y->len - 1) <= 128 * (int64_t)65535;
+               Y->n_paths * (int64_t)(Y->len - 1) <= sk::kCoefMaxCols;
     if (c.by_row) {
       auto row_of = [&](int64_t r) -> int64_t {
         if (!a.tri) return r / a.runs_per_row;

@@ -221,6 +221,8 @@ struct CoefArgs {
   int64_t row0, rows;       // launch holds (Grams with a uniform y batch, not refined); else runs
   float scale;              // 2^-(2 lam + 1) / rep^2
 };
+// Most columns of a stream: tiles of 128 in a grid's second dimension.
+constexpr int64_t kCoefMaxCols = 128 * (int64_t)65535;
 void* coef_sweep_fn(bool implicit, int lam, int R, int ng);
 // Floats of one wave's coefficient slots for runs of total_cols columns.
 int64_t coef_wave_floats(int64_t total_cols, int R, int lam, int ng);

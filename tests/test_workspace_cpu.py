@@ -35,3 +35,12 @@ def test_gram_of_one_wave_paths(lam, d, nx, ny, lx, ly):
     rep = 1 << max(lam - 3, 0)
     rows = (nx * (lx - 1) + ny * (ly - 1)) * rep + 4 * 128
     assert need(_lib.SK_OP_GRAM, nx, lx, ny, ly, d, lam) <= rows * ((d + 3) // 4 * 4) * 4 + 4096
+
+
+# Wide batches (above 16 channels): a run's columns stay within a grid's second
+# dimension (65535 tiles of 128), so a wave's slots are at most those of one such run.
+@pytest.mark.parametrize("nx,ny,ly", [(16384, 64, 1 << 18), (40000, 60, 1 << 19)])
+def test_wide_gram_of_long_streams(nx, ny, ly):
+    inc = (nx + ny * (ly - 1) + 4 * 128) * 20 * 4
+    slots = (128 * 65535 + 64 + 8) * 64 * 4
+    assert need(_lib.SK_OP_GRAM, nx, 2, ny, ly, 17, 0) <= inc + slots + (1 << 20)
