@@ -34,6 +34,7 @@ struct GradArgs {
   int32_t nseg_max;         // segments of the longest task
   int32_t ck_every;         // reversing kernel: segments per checkpoint,
   int32_t nck_max;          // ... and checkpoints of the longest task
+  double huge;              // ... and the node value from which a task is handed back unseen
   int64_t cols_max;         // coarse columns of the longest task
   double* part_x;           // [nx][runs_per_row][mrows][dim]: x-side increment gradients
   double* part_y;           // [nx][ny][nrows][dim]: y-side increment gradients

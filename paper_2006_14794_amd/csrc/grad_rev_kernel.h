@@ -201,7 +201,8 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
     const float* __restrict__ xinc = a.incx + first_row(a.x_start, a.x_len, ia) * DP;
     const float* __restrict__ ycol = a.incy + first_row(a.y_start, a.y_len, b0) * DP;
     double* __restrict__ pyt = YS ? a.part_y + ((int64_t)ia * a.ny + b0) * a.nrows * D : nullptr;
-    bool bad = false;
+    bool bad = false;      // this lane met nodes that differ too much, or will
+    bool give_up = false;  // (uniform) some lane did
 
     // columns of group q as the staging loops (any lane, any group) see them
     auto group_total = [&](int q) -> int32_t {
@@ -307,7 +308,7 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
     };
 
     // ---------------- forward pass: bands top to bottom ----------------
-    for (int band = 0; band < nb; ++band) {
+    for (int band = 0; band < nb && !give_up; ++band) {
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // hand_f of the band above
       const bool top = band == 0, last = band == nb - 1;
       const int p0 = ((band * GL + lg) * R - off) >> LAM;  // floor; < 0 for virtual rows
@@ -414,9 +415,14 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
           const uint32_t c0 = (uint32_t)(k * (R + 1) * 64 + lane);
 #pragma unroll
           for (int r = 0; r <= R; ++r) at(pn, c0 + r * 64) = spe[r * 64 + lane];
+          bad = bad || fabs(spe[R * 64 + lane]) > a.huge;
         }
         // the state after every ck_every-th segment and the last one
         if ((seg + 1) % a.ck_every == 0 || seg + 1 == nseg) {
+          if (__ballot(bad || fabs(u[R - 1]) > a.huge) != 0) {
+            give_up = true;
+            break;
+          }
           const uint32_t c0 = (uint32_t)(seg / a.ck_every * KS * 64 + lane);
 #pragma unroll
           for (int r = 0; r < R - 1; ++r) at(ck, c0 + r * 64) = u[r];
@@ -430,7 +436,7 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
     }
 
     // ---------------- reverse pass: bands bottom to top ----------------
-    for (int band = nb - 1; band >= 0; --band) {
+    for (int band = give_up ? -1 : nb - 1; band >= 0; --band) {
       // checkpoints, hand_f, hand_a, part_y
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
       const bool top = band == 0, last = band == nb - 1;
@@ -563,6 +569,9 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
           if (seg + 1 < nseg) {
 #pragma unroll
             for (int r = 0; r < R; ++r) bad = bad || drifted(kr[r], pk[r == 0 ? R - 1 + S : r - 1]);
+            // (or at a pair's end since the last checkpoint) the task is handed back:
+            // this segment is its last (leaving the loops here costs 2 % more)
+            if (__ballot(bad) != 0) seg = band = 0;
           }
           kr[0] = pk[R - 1 + S];
 #pragma unroll
@@ -801,7 +810,7 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     }
-    if (__ballot(bad) != 0) {
+    if (give_up || __ballot(bad) != 0) {
       int32_t i = 0;
       if (lane == 0) i = atomicAdd(a.redo_count, 1);
       i = __builtin_amdgcn_readlane(i, 0);

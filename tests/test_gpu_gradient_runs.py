@@ -75,3 +75,22 @@ def test_built_in_runs(lam, lx, ly):
     X = lines(rng, 64, lx, [3], 8.4)
     Y = lines(rng, 96, ly, [1, 5, 40, 94], 8.4)
     check(X, Y, lam, f"built-in runs lam{lam} {lx}x{ly}")
+
+
+@pytest.mark.parametrize("scale", [8.4, 20.0])
+@pytest.mark.parametrize("lam,n,lx,ly", [(0, 30, 60, 60), (1, 12, 129, 40), (1, 70, 129, 40),
+                                         (1, 8, 300, 200)])
+def test_values_of_handed_back_tasks(lam, n, lx, ly, scale):
+    # the MMD's blocks take their values from the gradient's forward pass, which a
+    # handed-back task leaves where it meets the large nodes
+    rng = np.random.default_rng(lx + n)
+    X, Y = lines(rng, n, lx, [1, n - 1], scale), lines(rng, n + 2, ly, [2], scale)
+    val, _ = sk.sigkernel_mmd2(cuda(X), cuda(Y), lam, grad=True)
+    X, Y = X.astype(np.float64), Y.astype(np.float64)
+    Kxx, Kyy, Kxy = oracle.gram(X, X, lam), oracle.gram(Y, Y, lam), oracle.gram(X, Y, lam)
+    np.fill_diagonal(Kxx, 0.0)
+    np.fill_diagonal(Kyy, 0.0)
+    # the values are float32: 6e-8 of each term
+    size = np.abs(Kxx).sum() / (n * (n - 1)) + np.abs(Kyy).sum() / ((n + 2) * (n + 1)) \
+        + 2.0 * np.abs(Kxy).mean()
+    assert abs(float(val) - oracle.mmd2_unbiased(Kxx, Kyy, Kxy)) <= 2e-7 * size
