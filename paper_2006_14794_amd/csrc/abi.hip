@@ -133,7 +133,8 @@ int64_t device_simds() {
 // symmetric 100 of 120 points, d = 3, order 2, runs of 3, 169, and single pairs now,
 // 155).  A wave alone takes at least 30 beside its step's work (48 x 40 paths of 100
 // points, d = 5, order 1: two waves of single pairs per SIMD 46 us, one of runs of
-// two 60).
+// two 60), 45 where its lanes stream four different runs of y paths (15 x 4 paths of 30 and 285
+// points, d = 1, order 0: two rows on 16 lanes 65 us, one row on 64 lanes 55).
 // run: the tuned value or 0; ties go to the shorter run.  simds: of the device, or
 // kSimds where a workspace size depends on the shape.  (Both sides measured: sweep_fwd_kernel.h.)
 struct SweepShape {
@@ -145,9 +146,11 @@ struct SweepShape {
 // like two channels) instead of forming inner products.  kLift: the lifted sweep,
 // d + 25 per node (its distance, exponential and differences) and d + 10 per step.
 // Its wave alone on a SIMD issues at 0.85 of the rate of four (64 x 64 paths of 257
-// points, d = 9, order 1: 652 us, two per SIMD 566) and takes 200 per step however
-// little that holds (60 x 80 paths of 100 points, d = 5, order 1: four rows per
-// lane, one wave per SIMD 201 us, three 183; 16 rows, one wave 159).
+// points, d = 9, order 1: 652 us, two per SIMD 566), and what a step takes beside its
+// work, about 350 cycles, counts more the less it holds (one pair of 42 and 390 points,
+// d = 3, order 0: one row per lane 98 us the call, three rows on 16 lanes 145; 60 x 80
+// paths of 100 points, d = 5, order 1: four rows per lane, one wave per SIMD 201 us,
+// three 183; 16 rows, one wave 159).
 enum SweepKind { kPlain, kCoef, kLift };
 SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t n, int lam,
                               int d, bool implicit, bool sym, bool no_diag, int32_t run,
@@ -181,8 +184,9 @@ SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t
                         : at_once == 2 ? (kind == kLift ? 0.93 : 0.88)
                                        : (kind == kLift ? 0.85 : 0.73);
     double step = issue;
-    if (at_once == 1 && kind == kLift && step < 200.0) step = 200.0;
-    if (at_once == 1 && kind != kLift && step < 81.0) step = (step + 30.0) * rate;
+    if (at_once == 1 && kind == kLift) step = std::max(step, 62.0 + 0.7 * step);
+    if (at_once == 1 && kind != kLift)
+      step = std::max(step, (step + (ng > 1 && rpr > 1 ? 45.0 : 30.0)) * rate);
     const double cost = (double)per_simd * (double)(k * n + gl - 1) * step / rate;
     if (best.R == 0 || cost < best_cost) {
       best = SweepShape{R, ng, k};
@@ -214,8 +218,9 @@ SweepShape choose_sweep_shape(int64_t nx, int64_t ny, int64_t fine_rows, int64_t
     }
     if (any) break;
   }
-  if (run <= 0 && best.R > 0)
-    for (int64_t k = 1; k <= cap; ++k) consider(best.R, best.ng, k);
+  // (single pairs on a SIMD each: longer runs only take longer)
+  if (run <= 0 && best.R > 0 && pairs > simds * best.ng)
+    for (int64_t k = 2; k <= cap; ++k) consider(best.R, best.ng, k);
   return best;
 }
 

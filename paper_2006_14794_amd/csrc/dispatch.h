@@ -12,18 +12,9 @@ constexpr bool sweep_fits(int R, int LAM, int D) {
   return ((R >> LAM) > 0 ? (R >> LAM) : 1) * D <= 96 && R <= 32;
 }
 
-// The forward Gram sweep's rows per lane on 64 / ng lanes: whole coarse rows per
-// lane or whole lanes per coarse row, in steps of a quarter to a third so that
-// at least three quarters of the lanes' rows are real at most path lengths.
-constexpr bool forward_fits(int R, int LAM, int D, int ng) {
-  const int S = 1 << LAM;
-  if (!sweep_fits(R, LAM, D) || (R % S != 0 && S % R != 0)) return false;
-  return ng == 1 ? R >= 2 : (ng == 4 && R <= 16);
-}
-
 // Largest power-of-two rows per lane (at most 32) that sweep_fits allows.
-// The pipelined band kernel only runs when the tallest grid needs several
-// bands, which happens only at this height, so it is compiled at it alone.
+// The pipelined band kernel with a fitted top band is compiled at it alone: the
+// tallest grid of a ragged batch needs several bands only at this height.
 constexpr int max_fitting_rows(int LAM, int D) {
   int r = 0;
   for (int R = 1; R <= 32; R *= 2)
@@ -31,14 +22,36 @@ constexpr int max_fitting_rows(int LAM, int D) {
   return r;
 }
 
+// The forward Gram sweep's rows per lane on 64 / ng lanes: whole coarse rows per
+// lane or whole lanes per coarse row, in steps of a quarter to a third so that
+// at least three quarters of the lanes' rows are real at most path lengths, up to
+// `most`.  (The shape model picks every one of these somewhere: all of them turned up
+// in three million random Grams.)
+constexpr bool forward_steps(int R, int LAM, int ng, int most) {
+  const int S = 1 << LAM;
+  if ((R % S != 0 && S % R != 0) || R > most) return false;
+  return ng == 1 || (ng == 4 && R <= 16);
+}
+constexpr bool forward_fits(int R, int LAM, int D, int ng) {
+  return sweep_fits(R, LAM, D) &&
+         forward_steps(R, LAM, ng, ng == 1 ? max_fitting_rows(LAM, D) : 32);
+}
+
 // The lifted sweep keeps the x nodes (coarse rows + 1) instead of the
 // increments, plus the previous column's row differences.
 constexpr bool lifted_fits(int R, int LAM, int D) {
   return (((R >> LAM) > 0 ? (R >> LAM) : 1) + 1) * D <= 96 && R <= 32;
 }
+constexpr int max_lifted_rows(int LAM, int D) {
+  int r = 0;
+  for (int R = 1; R <= 32; R *= 2)
+    if (lifted_fits(R, LAM, D)) r = R;
+  return r;
+}
 // ... its heights and runs per wave as the plain sweep's.
 constexpr bool lifted_group_fits(int R, int LAM, int D, int ng) {
-  return lifted_fits(R, LAM, D) && forward_fits(R, LAM, D, ng);
+  return lifted_fits(R, LAM, D) &&
+         forward_steps(R, LAM, ng, ng == 1 ? max_lifted_rows(LAM, D) : 32);
 }
 
 template <class F, int R, int LAM>

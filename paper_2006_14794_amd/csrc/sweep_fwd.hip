@@ -57,11 +57,8 @@ bool forward_takes(int64_t fine_rows, int lam, int d) {
 }
 
 bool lifted_takes(int64_t fine_rows, int lam, int d) {
-  if (lam < 0 || lam > 3 || d < 1 || d > 16) return false;
-  int r = 0;
-  for (int R = 1; R <= kMaxRowsPerLane; R *= 2)
-    if (lifted_fits(R, lam, d)) r = R;
-  return fine_rows <= 64 * (int64_t)r;
+  return lam >= 0 && lam <= 3 && d >= 1 && d <= 16 &&
+         fine_rows <= 64 * (int64_t)max_lifted_rows(lam, d);
 }
 
 namespace {
