@@ -626,6 +626,9 @@ __attribute__((amdgpu_waves_per_eu(D <= 4 && LAM < 3 ? 2 : 1, 2))) void grad_ker
           if ((pe >> j) & 1u) {  // last column of a pair: nothing to the right
 #pragma unroll
             for (int r = 0; r < R; ++r) ar[r] = 0.0;
+            // (their factors are the next pair's, perhaps not finite)
+#pragma unroll
+            for (int c = 0; c < CR; ++c) gr[c] = 1.0;
             // the terminal cell (lane 63 of the last band, last row) receives
             // the seed through its below-right neighbour: a = 0 + 0 - (-w)
             prev_ab0 = (last && lane == 63) ? -pair_weight(a, ia, b0 + (g0 + j) / n) : 0.0;

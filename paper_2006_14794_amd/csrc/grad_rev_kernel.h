@@ -660,6 +660,9 @@ __attribute__((amdgpu_waves_per_eu(grad_rev_waves(R, LAM, D), 2))) void grad_rev
               kr[r] = spe[r * 64 + lane];
             }
             kc = spe[R * 64 + lane];
+            // (their factors are the next pair's, perhaps not finite)
+#pragma unroll
+            for (int c = 0; c < CR; ++c) gr[c] = 1.0;
             prev_ab0 = seed;
           }
           double gk[CR];
