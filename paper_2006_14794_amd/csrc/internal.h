@@ -153,6 +153,7 @@ struct PairArgs {
   const int32_t* count;     // device: pairs in this class (nullptr: n_pairs)
   int32_t n_pairs;
   int32_t* counter;         // device queue head (zeroed by an earlier kernel)
+  uint32_t units;           // compute units (set by the launch)
   double* bandbuf;          // per wave slot: band_stride doubles
   int64_t band_stride;
   float* out;               // out[pid]

@@ -40,18 +40,25 @@ __global__ __launch_bounds__(256) void pair_kernel(const PairArgs a) {
   const int32_t* __restrict__ order = a.order;
   if (order && a.order_base) order += *a.order_base;
 
-  // A wave's first pair is its slot's, so that as many pairs as SIMDs or fewer run
-  // on as many SIMDs (workgroups go round the compute units) and not where a wave
-  // happened to reach the queue first (the corrector's 1045 order-3 pairs of 256
-  // points on 2048 waves: predict 1.36 ms, 1.50 with every claim from the queue).
-  // Then one vector atomic per pair.
+  // A wave's first pair is its place's, so that as many pairs as SIMDs or fewer run
+  // on as many SIMDs and not where a wave happened to reach the queue first (the
+  // corrector's 1045 order-3 pairs of 256 points on 2048 waves: predict 1.36 ms, 1.50
+  // with every claim from the queue).  Places go round the compute units, as the
+  // workgroups do, then round each one's waves: few pairs have a compute unit each
+  // (42 order-3 pairs of 128 points, d = 12, on 260 waves: 169 us, 188 four to a
+  // unit; 503 of 257 points, d = 2, on 600: 396 and 466).  Then one vector atomic
+  // per pair.
+  const uint32_t layer = blockIdx.x / a.units, in = blockIdx.x - layer * a.units;
+  const uint32_t left = gridDim.x - layer * a.units;
+  const uint32_t place = layer * a.units * (blockDim.x >> 6) +
+                         (threadIdx.x >> 6) * (left < a.units ? left : a.units) + in;
   auto claim = [&]() __attribute__((always_inline)) {
     int32_t k = 0;
     if (lane == 0) k = atomicAdd(a.counter, 1);
     // scalar: the task loop's control flow is uniform
     return (int32_t)(gridDim.x * (blockDim.x >> 6)) + __builtin_amdgcn_readlane(k, 0);
   };
-  for (int32_t k = __builtin_amdgcn_readfirstlane((int32_t)slot); k < count; k = claim()) {
+  for (int32_t k = __builtin_amdgcn_readfirstlane((int32_t)place); k < count; k = claim()) {
     const int32_t pid = order ? order[k] : k;
     const int64_t ix = a.gram_ny ? pid / a.gram_ny : pid;
     const int64_t iy = a.gram_ny ? pid - ix * a.gram_ny : pid;

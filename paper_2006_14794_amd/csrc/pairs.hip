@@ -279,7 +279,9 @@ hipError_t launch_persistent(int kind, const PairArgs& a, int lam, int R, int d,
   int64_t waves = (int64_t)cus * blocks_per_cu * 4;
   if (waves > max_waves) waves = max_waves;  // max_waves: a multiple of 4 (wave slots)
   const int64_t blocks = waves / 4 > 0 ? waves / 4 : 1;
-  hipLaunchKernelGGL(f, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  PairArgs b = a;
+  b.units = cus > 0 ? (uint32_t)cus : 1u;
+  hipLaunchKernelGGL(f, dim3((unsigned)blocks), dim3(256), 0, stream, b);
   return hipGetLastError();
 }
 }  // namespace
