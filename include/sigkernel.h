@@ -173,16 +173,20 @@ size_t sigkernel_gram_noalloc_max_bytes(void);
  *    the points).  A pair with a broken path (see sk_paths) contributes NaN
  *    to the gradient of its paths; point rows of a ragged batch that belong
  *    to no valid path receive NaN.
- *  - Any x length within the order limit: x paths taller than one band of
- *    256 fine rows are swept in bands.
- *  - Method: the forward pass saves the wavefront state every few steps
- *    (checkpoints, about 0.9 bytes per fine cell at order 1) and the adjoint
- *    recomputes each stretch of forward values from its checkpoint, bitwise
- *    as the forward computed them, instead of storing them.
+ *  - Any x length within the order limit: x paths taller than one band
+ *    (256 or 512 fine rows) are swept in bands.
+ *  - Method: the forward pass saves the wavefront state every few dozen steps
+ *    (checkpoints) and the adjoint rebuilds the forward values between them by
+ *    running the scheme backwards.  Where the rebuilt values meet saved ones
+ *    (checkpoints, a pair's first column) they are compared, and a task in
+ *    which they differ by more than 2^-28 relative is done again by recomputing
+ *    the forward values from closer checkpoints, bitwise as the forward pass
+ *    computed them.  Runs of many short y paths are recomputed in the first
+ *    place, where that is cheaper.
  *  - Workspace: sigkernel_workspace_bytes(SK_OP_GRAM_BACKWARD, ...): the
- *    checkpoints of at most 2048 tasks in flight (a task is a run of pairs
- *    sharing one x path, or one pair of a ragged batch) and the increment
- *    gradients of every pair, in double.
+ *    checkpoints and band rows of at most 2048 tasks in flight (a task is a
+ *    run of pairs sharing one x path, or one pair of a ragged batch) and the
+ *    increment gradients of every pair, in double.
  */
 sk_status sigkernel_gram_backward(const sk_paths *X, const sk_paths *Y, int32_t dyadic_order,
                                   uint32_t flags, const float *dK, float *dX, float *dY,

@@ -41,7 +41,8 @@ struct GradArgs {
   int32_t mrows, nrows;     // x_len - 1, y_len - 1
   // tasks whose rebuilt forward nodes differed too much (grad_rev_kernel.h):
   // that kernel appends them here, and grad_kernel.h takes its tasks from this
-  // list alone (nullptr there: all n_tasks tasks)
+  // list alone (nullptr there: all n_tasks tasks, where the plan has no
+  // reversing launch before it)
   int32_t* redo;
   int32_t* redo_count;      // zeroed before the launches
 };

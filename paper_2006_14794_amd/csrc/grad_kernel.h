@@ -44,6 +44,9 @@
 //  * Inputs of a segment (y rows, the neighbouring bands' rows) are staged
 //    in LDS one segment ahead; outputs for the neighbouring bands are staged
 //    in LDS and written out once per segment.
+// Where it runs: for the tasks that the reversing kernel (grad_rev_kernel.h)
+// hands back, and instead of that kernel for runs of many short y paths, where
+// the pair ends cost more there than the recomputation here.
 // HBM traffic per fine cell: the checkpoints, 8 (R + 2^lambda) /
 // (R 2^lambda C) bytes written once and read once, instead of a stored cell
 // sum per fine cell.

@@ -15,12 +15,13 @@
 // instructions per 8 fine cells against 150 here at four rows per lane and 120
 // at eight.  Bound: instruction issue (about 80 % of it at two waves per
 // SIMD).  Measured, 64 x 64 pairs of 512 points, d = 4, order 1, x side only:
-// 2.26 ms against 4.05; both sides of the 2016 pairs of a symmetric Gram:
-// 1.41 against 2.67; 48 x 40 pairs of 100 points, d = 5, both sides: 0.169
+// 2.07 ms against 4.05; both sides of the 2016 pairs of a symmetric Gram:
+// 1.24 against 2.67; 48 x 40 pairs of 100 points, d = 5, both sides: 0.169
 // against 0.354.  Steps of the first: 3.0 ms with four rows per lane; 2.35
 // with eight, the checkpoints read without prefetch (their registers) and
 // only every fourth segment; 2.26 with the y-side sums in LDS, pair ends by
-// step index and the cell factor handed over instead of the coefficient.
+// step index and the cell factor handed over instead of the coefficient; 2.04
+// to 2.15 with those sums laid out by channel.
 //
 // What the reverse pass needs of the forward one:
 //  * the nodes right of its first column: each lane's state after every

@@ -185,7 +185,7 @@ hipError_t launch_pair_plan(const PairPlanArgs& p, hipStream_t stream);
 hipError_t launch_band_plan(const PairPlanArgs& p, int rows_per_lane, int32_t* task_base,
                             int32_t* task_counter, hipStream_t stream);
 // The pipelined band kernel over those tasks (persistent, like launch_pairs),
-// compiled only at the largest rows per lane that fits.  fit_top: each pair's
+// at any rows per lane that fits.  fit_top: each pair's
 // top band takes R/4, R/2 or R rows per lane by its rows; else every band
 // takes R.
 hipError_t launch_pair_bands(const PairArgs& a, int lam, int rows_per_lane, int dim,
